@@ -234,6 +234,10 @@ void free_graph_arrays(mlmq_graph* g) {
   (void)hipFree(g->d_off_ord);
   (void)hipFree(g->d_adj_ord);
   (void)hipFree(g->d_ord_of);
+  (void)hipFree(g->d_ioff);
+  (void)hipFree(g->d_iadj);
+  g->d_ioff = nullptr;
+  g->d_iadj = nullptr;
   g->d_off = g->d_off_ord = nullptr;
   g->d_adj = g->d_adj_ord = nullptr;
   g->d_ord_of = nullptr;
@@ -331,10 +335,12 @@ extern "C" int mlmq_graph_create(int32_t n, int64_t m, const int32_t* row_offset
     adj.shrink_to_fit();
     e = upload_degree_order(g.get(), hoff, hcol, hw);
   }
+  if (e == hipSuccess) e = step_prepare(g.get());
   if (e != hipSuccess) {
     free_graph_arrays(g.get());
     return hip_fail(e, "uploading graph");
   }
+  (void)resolve_config(g.get(), nullptr, &g->sel_config);
   *out = g.release();
   return MLMQ_OK;
 }
@@ -824,6 +830,11 @@ int run_single(const mlmq_graph* g, uint32_t source, uint32_t* dist_out, const m
   // power-law graphs are solved on their degree-ordered copy, whose labels
   // are gathered back into the caller's order at the end
   const bool ordered = g->d_ord_of != nullptr;
+  if (g->step_ready && is_default_choice(g, c, unit_weights)) {
+    bool finished = false;
+    rc = run_step(g, source, dist_out, c, unit_weights, dev_out, &finished);
+    if (finished) return rc;
+  }
   LaunchShape shape;
   rc = launch_shape(c, c.l1_type == MLMQ_L1_NONE ? 64u : c.l1_cap, c.l1_type == MLMQ_L1_NEARFAR,
                     c.l2_type == MLMQ_L2_BUCKET, c.l2_type == MLMQ_L2_PQ, &shape);

@@ -33,6 +33,12 @@ struct mlmq_graph {
   bool has_tuned = false;
   mlmq_config tuned{};
   int32_t sel_template = -1;  // the selector's top template (-1: the feature heuristic)
+  mlmq_config sel_config{};   // that template as a configuration for this graph
+  // stepping solve (mlmq_step.cpp): in-rows of the graph that plain solves run
+  // on; both its out-rows and these are in ascending weight class
+  bool step_ready = false;
+  int32_t* d_ioff = nullptr;   // [n+1]
+  uint64_t* d_iadj = nullptr;  // [m]
 };
 
 namespace mlmq {
@@ -99,6 +105,13 @@ std::string describe_query_state(const QueryDesc& d, const uint32_t* d_beats, ui
 void fill_stats(mlmq_stats* st, const QueryCtrl& h, double ms, double worker_ms, uint32_t grid, uint32_t retries);
 int run_single(const mlmq_graph* g, uint32_t source, uint32_t* dist_out, const mlmq_config& c,
                bool unit_weights = false);
+// Whether c is the library's own choice for g (a solve may then run without queues).
+bool is_default_choice(const mlmq_graph* g, const mlmq_config& c, bool unit_weights);
+// Rows in ascending weight class and a transposed copy, where g suits the stepping solve.
+hipError_t step_prepare(mlmq_graph* g);
+// Stepping solve; *finished = false: nothing was decided, the queue worker must solve.
+int run_step(const mlmq_graph* g, uint32_t source, uint32_t* dist_out, const mlmq_config& c, bool unit_weights,
+             bool dev_out, bool* finished);
 // What the host watchdog snapshots when a launch overruns its deadline.
 struct WatchdogView {
   const QueryCtrl* d_ctrl = nullptr;  // first query's control block

@@ -1,0 +1,325 @@
+// Host side of the stepping solve: preparation of a graph's rows, the rule
+// that picks the graphs, and the loop that keeps the device a few launches
+// ahead until a step reports the end.
+
+#include <hip/hip_runtime.h>
+
+#include <algorithm>
+#include <atomic>
+#include <chrono>
+#include <cmath>
+#include <cstring>
+#include <thread>
+
+#include "../../include/mlmq.h"
+#include "mlmq_api_internal.h"
+#include "mlmq_internal.h"
+#include "mlmq_step.h"
+
+using namespace mlmq;
+
+namespace mlmq {
+
+namespace {
+
+size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
+
+// Launches kept ahead of the last step known to have begun: enough that the
+// device never waits for the host (a launch costs the host 3 us, the shortest
+// step 5 us), few enough that the ones queued past the end cost little.
+constexpr uint32_t kAhead = 5;
+
+uint32_t class_shift(uint32_t max_w) {
+  uint32_t bits = 0;
+  while (bits < 32 && (max_w >> bits)) ++bits;
+  return bits > 8 ? bits - 8 : 0;
+}
+
+struct StepLayout {
+  size_t rec, shard, stats, list0, list1, settled, task0, task1, lab, out, bytes;
+  uint32_t cap, task_cap;
+};
+
+StepLayout step_layout(const mlmq_graph* g, bool own_lab, bool own_out) {
+  StepLayout l;
+  // A segment takes its share of all vertices and a quarter more, and what
+  // the waves' last, partly filled blocks may add.
+  l.cap = (uint32_t)((uint64_t)g->n / kStepSegs + (uint64_t)g->n / (4 * kStepSegs) + 8192u);
+  // a row above the limit is expanded once per step
+  l.task_cap = (uint32_t)(g->m / (kStepChunk / 2) + 64);
+  const size_t list = 8ull * kStepSegs * l.cap;
+  size_t o = 0;
+  auto take = [&o](size_t bytes) {
+    const size_t at = o;
+    o = align_up(o + bytes, 256);
+    return at;
+  };
+  l.rec = take(sizeof(StepRec) * kStepMax);
+  l.shard = take(sizeof(StepShard) * kStepSegs);
+  l.stats = take(sizeof(StepStats) * kStepSegs);
+  l.list0 = take(list);
+  l.list1 = take(list);
+  l.settled = take(list);
+  l.task0 = take(16ull * l.task_cap);
+  l.task1 = take(16ull * l.task_cap);
+  l.lab = take(own_lab ? 4ull * g->n : 0);
+  l.out = take(own_out ? 4ull * g->n : 0);
+  l.bytes = o;
+  return l;
+}
+
+// Launches steps until one reports the end (true), the limit is reached or
+// the deadline passes (false, *late); the stream is idle afterwards.
+hipError_t drive(const StepArgs& a, uint32_t blocks, uint32_t limit, uint32_t timeout_ms, hipStream_t stream, bool* done,
+                 bool* late) {
+  using clk = std::chrono::steady_clock;
+  const auto end = clk::now() + std::chrono::milliseconds(timeout_ms);
+  StepHost* const h = a.host;
+  uint32_t issued = 0, spins = 0;
+  *done = *late = false;
+  for (;;) {
+    const uint32_t state = __atomic_load_n(&h->state, __ATOMIC_ACQUIRE);
+    if (state) {
+      *done = state == 1;
+      break;
+    }
+    const uint32_t begun = __atomic_load_n(&h->begun, __ATOMIC_RELAXED);
+    if (begun + 1 >= limit) break;
+    if (issued + 1 < limit && issued < begun + kAhead) {
+      const hipError_t e = launch_step(a, ++issued, blocks, stream);
+      if (e != hipSuccess) return e;
+      continue;
+    }
+    if ((++spins & 1023u) == 0) {
+      if (clk::now() > end) {
+        *late = true;
+        break;
+      }
+      const hipError_t e = hipStreamQuery(stream);
+      if (e == hipSuccess && issued + 1 >= limit) break;  // every step ran
+      if (e != hipSuccess && e != hipErrorNotReady) return e;
+    }
+#if defined(__x86_64__)
+    __builtin_ia32_pause();
+#endif
+  }
+  hipError_t e;
+  while ((e = hipStreamQuery(stream)) == hipErrorNotReady) {
+  }
+  if (e == hipSuccess && !*done && __atomic_load_n(&h->state, __ATOMIC_ACQUIRE) == 1) *done = true;
+  return e;
+}
+
+void graph_args(const mlmq_graph* g, StepArgs* a) {
+  const bool ordered = g->d_ord_of != nullptr;
+  a->off = ordered ? g->d_off_ord : g->d_off;
+  a->adj = ordered ? g->d_adj_ord : g->d_adj;
+  a->ioff = g->d_ioff;
+  a->iadj = g->d_iadj;
+  a->ord_of = ordered ? g->d_ord_of : nullptr;
+  a->n = (uint32_t)g->n;
+  a->cls_mask = (1u << class_shift(g->max_w)) - 1u;
+  a->max_w = g->max_w;
+  a->m = (uint64_t)g->m;
+  a->phase_cost = 1u << 20;  // three or four launches of 6 us at 50 G edges a second
+  // Width of a distance step, as a multiple of the weight below which a vertex
+  // has one edge on average. Skewed graphs: wide enough that the vertices most
+  // edges end at are settled in the first step and the rest pull (RMAT-23:
+  // 1 / 1.5 / 2 / 3 -> 1.13 / 0.98 / 1.14 / 1.32 ms; RMAT-20 0.71 / 0.32 /
+  // 0.35 / 0.44). Others: ordering work against the launches of a step
+  // (uniform 4 M vertices, 33 M edges: 4 / 8 / 16 / 32 -> 2.04 / 1.70 / 1.71 /
+  // 1.72 ms; 150,001 vertices, 0.3 M edges: 8 / 32 / 64 -> 0.69 / 0.46 / 0.39).
+  const double deg = std::max(1.0, g->features.avg_deg), m = (double)g->m;
+  double f;
+  if (g->features.std_deg > g->features.avg_deg)
+    f = 1.5 * std::min(3.0, std::max(std::min(1.0, std::max(0.25, deg / 30.0)), std::sqrt(8.4e6 / m)));
+  else
+    f = 8.0 * std::min(32.0, std::max(1.0, std::sqrt(3.4e7 / m)));
+  a->delta = (uint32_t)std::min(1e9, std::max(1.0, f * g->features.avg_w / deg));
+}
+
+uint32_t step_blocks(const mlmq_graph* g) {
+  // one wave per 64 vertices or 512 edges, up to sixteen waves per CU (with
+  // thirty-two the launch and the list counters cost more than the extra loads
+  // in flight gain: RMAT-23 1.00 ms against 0.93, uniform 4 M 1.67 against 1.36)
+  const uint64_t waves = (uint64_t)g->n / 64 + (uint64_t)g->m / 512;
+  return (uint32_t)std::min<uint64_t>(4ull * device_info()->cus, std::max<uint64_t>(16, waves / kStepWaves));
+}
+
+}  // namespace
+
+// Whether two configurations ask for the same queues.
+static bool same_queues(const mlmq_config& a, const mlmq_config& b) {
+  return a.l0_rows == b.l0_rows && a.l1_type == b.l1_type && a.l2_type == b.l2_type && a.relax_mode == b.relax_mode &&
+         a.l1_cap == b.l1_cap && a.l1_flush_wb == b.l1_flush_wb && a.delta1 == b.delta1 &&
+         a.delta2_log2 == b.delta2_log2 && a.bmax == b.bmax && a.bnum == b.bnum && a.th_v == b.th_v &&
+         a.th_hub == b.th_hub && a.hub_chunk == b.hub_chunk && a.wg_size == b.wg_size && a.grid_wgs == b.grid_wgs &&
+         a.l2_capacity == b.l2_capacity && a.donate_min == b.donate_min && a.pnum == b.pnum;
+}
+
+// The queue configuration of a graph left to the library's choice is a
+// default, not a request: a solve that carries it may run without queues. Any
+// other configuration gets the queues it describes, and so does a deadline too
+// fine for the host to watch (the queue worker's waves watch it themselves).
+bool is_default_choice(const mlmq_graph* g, const mlmq_config& c, bool unit_weights) {
+  if (c.timeout_ms && c.timeout_ms < 50) return false;
+  mlmq_config d = g->sel_config;
+  if (unit_weights) {
+    d.delta1 = 1;
+    d.delta2_log2 = 0;
+  }
+  return same_queues(c, d);
+}
+
+hipError_t step_prepare(mlmq_graph* g) {
+  g->step_ready = false;
+  // meshes and road-like graphs (a handful of edges at every vertex) are deep
+  if (g->m == 0 || g->features.max_deg <= 8) return hipSuccess;
+  const uint32_t n = (uint32_t)g->n, m = (uint32_t)g->m;
+  const bool ordered = g->d_ord_of != nullptr;
+  const int32_t* off = ordered ? g->d_off_ord : g->d_off;
+  uint64_t** adj = ordered ? &g->d_adj_ord : &g->d_adj;
+  const uint32_t shift = class_shift(g->max_w);
+  uint64_t *sorted = nullptr, *raw = nullptr;
+  uint32_t* scratch = nullptr;
+  hipError_t e = hipMalloc(&sorted, 8ull * m);
+  if (e == hipSuccess) e = hipMalloc(&raw, 8ull * m);
+  if (e == hipSuccess) e = hipMalloc(&scratch, 4ull * (n + 1ull + n / 4096 + 2));
+  if (e == hipSuccess) e = hipMalloc(&g->d_ioff, 4ull * (n + 1ull));
+  if (e == hipSuccess) e = hipMalloc(&g->d_iadj, 8ull * m);
+  if (e == hipSuccess) e = launch_sort_rows(off, *adj, sorted, n, shift, nullptr);
+  if (e == hipSuccess) e = launch_transpose(off, sorted, n, m, g->d_ioff, raw, scratch, nullptr);
+  if (e == hipSuccess) e = launch_sort_rows(g->d_ioff, raw, g->d_iadj, n, shift, nullptr);
+  if (e == hipSuccess) e = hipStreamSynchronize(nullptr);
+  (void)hipFree(raw);
+  (void)hipFree(scratch);
+  if (e != hipSuccess) {
+    (void)hipFree(sorted);
+    (void)hipFree(g->d_ioff);
+    (void)hipFree(g->d_iadj);
+    g->d_ioff = nullptr;
+    g->d_iadj = nullptr;
+    if (e != hipErrorOutOfMemory) return e;
+    (void)hipGetLastError();  // no room for the second copy: the graph keeps to the queue worker
+    return hipSuccess;
+  }
+  (void)hipFree(*adj);
+  *adj = sorted;
+  g->step_ready = true;
+  return hipSuccess;
+}
+
+int run_step(const mlmq_graph* g, uint32_t source, uint32_t* dist_out, const mlmq_config& c, bool unit_weights,
+             bool dev_out, bool* finished) {
+  hipStream_t stream = reinterpret_cast<hipStream_t>(c.stream);
+  const bool ordered = g->d_ord_of != nullptr;
+  const StepLayout l = step_layout(g, ordered || !dev_out, ordered && !dev_out);
+  *finished = true;
+  Slab* slab = nullptr;
+  const size_t desc_off = l.bytes;
+  const size_t flag_off = align_up(desc_off + sizeof(QueryDesc), 256);
+  int rc = slab_acquire(flag_off + 256, sizeof(StepHost) + sizeof(QueryDesc) + 64, &slab);
+  if (rc == MLMQ_ERR_OUT_OF_MEMORY) {
+    *finished = false;  // the queues may need less
+    return MLMQ_OK;
+  }
+  if (rc) return rc;
+  char* const base = static_cast<char*>(slab->dev);
+  StepHost* const host = static_cast<StepHost*>(slab->host);
+  std::memset(host, 0, sizeof(*host));
+  StepArgs a;
+  std::memset(&a, 0, sizeof(a));
+  graph_args(g, &a);
+  uint32_t* const d_final = dev_out ? dist_out : reinterpret_cast<uint32_t*>(base + (ordered ? l.out : l.lab));
+  a.lab = ordered || !dev_out ? reinterpret_cast<uint32_t*>(base + l.lab) : dist_out;
+  a.out = d_final;
+  a.rec = reinterpret_cast<StepRec*>(base + l.rec);
+  a.shard = reinterpret_cast<StepShard*>(base + l.shard);
+  a.stats = c.stats_out ? reinterpret_cast<StepStats*>(base + l.stats) : nullptr;
+  a.list[0] = reinterpret_cast<uint64_t*>(base + l.list0);
+  a.list[1] = reinterpret_cast<uint64_t*>(base + l.list1);
+  a.settled = reinterpret_cast<uint64_t*>(base + l.settled);
+  a.task[0] = reinterpret_cast<uint64_t*>(base + l.task0);
+  a.task[1] = reinterpret_cast<uint64_t*>(base + l.task1);
+  a.host = host;
+  a.source = ordered ? g->h_ord_of[source] : source;
+  a.cap = l.cap;
+  a.task_cap = l.task_cap;
+  a.unit_w = unit_weights ? 1u : 0u;
+  a.want_max = g->overflow_safe || unit_weights ? 0u : 1u;
+  const uint32_t blocks = step_blocks(g);
+  const uint32_t timeout_ms = c.timeout_ms ? c.timeout_ms : 60000;
+  hipEvent_t ev0 = nullptr, evw = nullptr, ev1 = nullptr;
+  hipError_t e = hipSuccess;
+  if (c.stats_out) {
+    e = hipEventCreate(&ev0);
+    if (e == hipSuccess) e = hipEventCreate(&evw);
+    if (e == hipSuccess) e = hipEventCreate(&ev1);
+    if (e == hipSuccess) e = hipEventRecord(ev0, stream);
+  }
+  if (e == hipSuccess) e = launch_step_init(a, std::max(64u, blocks), stream);
+  if (e == hipSuccess && evw) e = hipEventRecord(evw, stream);
+  bool done = false, late = false;
+  if (e == hipSuccess) e = drive(a, blocks, kStepMax, timeout_ms, stream, &done, &late);
+  if (e == hipSuccess && ev1) e = hipEventRecord(ev1, stream);
+  float ms = 0, wms = 0;
+  if (e == hipSuccess && ev1) e = hipEventSynchronize(ev1);
+  if (e == hipSuccess && ev1) e = hipEventElapsedTime(&ms, ev0, ev1);
+  if (e == hipSuccess && ev1) e = hipEventElapsedTime(&wms, evw, ev1);
+  if (ev0) (void)hipEventDestroy(ev0);
+  if (evw) (void)hipEventDestroy(evw);
+  if (ev1) (void)hipEventDestroy(ev1);
+  if (e != hipSuccess) {
+    slab_release(slab);
+    return hip_fail(e, "stepping solve");
+  }
+  if (!done) {
+    slab_release(slab);
+    if (late) return set_error(MLMQ_ERR_TIMEOUT, "the solve overran its timeout of %u ms", timeout_ms);
+    *finished = false;  // too deep or a list ran over: the queue worker takes it
+    return MLMQ_OK;
+  }
+  if (a.want_max && (uint64_t)host->max_label + g->max_w >= kInf) {
+    // Some candidate may have been too large to store: exact test, an edge
+    // from a finite label to an unreachable one.
+    QueryDesc* h_desc = reinterpret_cast<QueryDesc*>(host + 1);
+    uint32_t* h_flag = reinterpret_cast<uint32_t*>(h_desc + 1);
+    std::memset(h_desc, 0, sizeof(*h_desc));
+    h_desc->off = a.off;
+    h_desc->adj = a.adj;
+    h_desc->dist = a.lab;
+    h_desc->n = a.n;
+    QueryDesc* d_desc = reinterpret_cast<QueryDesc*>(base + desc_off);
+    uint32_t* d_flag = reinterpret_cast<uint32_t*>(base + flag_off);
+    *h_flag = 0;
+    e = hipMemcpyAsync(d_desc, h_desc, sizeof(QueryDesc), hipMemcpyHostToDevice, stream);
+    if (e == hipSuccess) e = hipMemcpyAsync(d_flag, h_flag, 4, hipMemcpyHostToDevice, stream);
+    if (e == hipSuccess) e = launch_overflow_check(d_desc, d_flag, stream);
+    if (e == hipSuccess) e = hipMemcpyAsync(h_flag, d_flag, 4, hipMemcpyDeviceToHost, stream);
+    if (e == hipSuccess) e = hipStreamSynchronize(stream);
+    if (e != hipSuccess) {
+      slab_release(slab);
+      return hip_fail(e, "overflow check");
+    }
+    if (*h_flag) rc = set_error(MLMQ_ERR_DISTANCE_OVERFLOW, "a reachable distance does not fit below 2^32-1");
+  }
+  if (!dev_out) {
+    e = hipMemcpyAsync(dist_out, d_final, 4ull * g->n, hipMemcpyDeviceToHost, stream);
+    if (e == hipSuccess) e = hipStreamSynchronize(stream);
+    if (e != hipSuccess) rc = hip_fail(e, "copying distances");
+  }
+  if (c.stats_out) {
+    QueryCtrl t;
+    std::memset(&t, 0, sizeof(t));
+    t.stats[kCtExpansions] = host->stats[0];
+    t.stats[kCtStale] = host->stats[1];
+    t.stats[kCtEdges] = host->stats[2];
+    t.stats[kCtPushes] = host->stats[3];
+    t.stats[kCtAtomics] = host->stats[4];
+    fill_stats(c.stats_out, t, ms, wms, blocks * kStepWaves, 0);
+  }
+  slab_release(slab);
+  return rc;
+}
+
+}  // namespace mlmq
