@@ -70,6 +70,7 @@ const DeviceInfo* device_info() {
       rate_khz = 100000;
     info.ticks_per_ms = (uint64_t)rate_khz;
     info.lds_per_wg = (size_t)p.sharedMemPerBlock;
+    info.lds_per_cu = std::max((size_t)p.maxSharedMemoryPerMultiProcessor, info.lds_per_wg);
     snprintf(info.name, sizeof(info.name), "%s", p.gcnArchName);
   });
   return &info;
@@ -236,6 +237,8 @@ void free_graph_arrays(mlmq_graph* g) {
   (void)hipFree(g->d_ord_of);
   (void)hipFree(g->d_ioff);
   (void)hipFree(g->d_iadj);
+  tile_destroy(g->tiles);
+  g->tiles = nullptr;
   g->d_ioff = nullptr;
   g->d_iadj = nullptr;
   g->d_off = g->d_off_ord = nullptr;
@@ -335,7 +338,8 @@ extern "C" int mlmq_graph_create(int32_t n, int64_t m, const int32_t* row_offset
     adj.shrink_to_fit();
     e = upload_degree_order(g.get(), hoff, hcol, hw);
   }
-  if (e == hipSuccess) e = step_prepare(g.get());
+  if (e == hipSuccess) e = tile_prepare(g.get(), hoff, hcol);
+  if (e == hipSuccess && !g->tiles) e = step_prepare(g.get());
   if (e != hipSuccess) {
     free_graph_arrays(g.get());
     return hip_fail(e, "uploading graph");
@@ -830,9 +834,9 @@ int run_single(const mlmq_graph* g, uint32_t source, uint32_t* dist_out, const m
   // power-law graphs are solved on their degree-ordered copy, whose labels
   // are gathered back into the caller's order at the end
   const bool ordered = g->d_ord_of != nullptr;
-  if (g->step_ready && is_default_choice(g, c, unit_weights)) {
+  if (bulk_solves(g, c, unit_weights)) {
     bool finished = false;
-    rc = run_step(g, source, dist_out, c, unit_weights, dev_out, &finished);
+    rc = run_bulk(g, source, dist_out, c, unit_weights, dev_out, &finished);
     if (finished) return rc;
   }
   LaunchShape shape;

@@ -12,6 +12,8 @@
 #include "../../include/mlmq.h"
 #include "mlmq_internal.h"
 
+struct mlmq_tiles;  // tiled copy of a graph (mlmq_tile.cpp)
+
 // Device-resident graph (the opaque mlmq_graph of the C ABI).
 struct mlmq_graph {
   int32_t n = 0;
@@ -39,6 +41,7 @@ struct mlmq_graph {
   bool step_ready = false;
   int32_t* d_ioff = nullptr;   // [n+1]
   uint64_t* d_iadj = nullptr;  // [m]
+  mlmq_tiles* tiles = nullptr;  // tiled copy (null: the graph does not fall into tiles)
 };
 
 namespace mlmq {
@@ -49,6 +52,7 @@ struct DeviceInfo {
   int cus = 0;
   uint64_t ticks_per_ms = 100000;
   size_t lds_per_wg = 65536;
+  size_t lds_per_cu = 65536;
   char name[64] = {0};
 };
 
@@ -109,8 +113,14 @@ int run_single(const mlmq_graph* g, uint32_t source, uint32_t* dist_out, const m
 bool is_default_choice(const mlmq_graph* g, const mlmq_config& c, bool unit_weights);
 // Rows in ascending weight class and a transposed copy, where g suits the stepping solve.
 hipError_t step_prepare(mlmq_graph* g);
-// Stepping solve; *finished = false: nothing was decided, the queue worker must solve.
-int run_step(const mlmq_graph* g, uint32_t source, uint32_t* dist_out, const mlmq_config& c, bool unit_weights,
+// Tiled copy of g, where it falls into tiles (off, col: host CSR).
+hipError_t tile_prepare(mlmq_graph* g, const int32_t* off, const int32_t* col);
+void tile_destroy(mlmq_tiles* t);
+// Whether a solve on g with c runs as a sequence of launches (stepping or
+// tiled) instead of the queue worker.
+bool bulk_solves(const mlmq_graph* g, const mlmq_config& c, bool unit_weights);
+// Such a solve; *finished = false: nothing was decided, the queue worker must solve.
+int run_bulk(const mlmq_graph* g, uint32_t source, uint32_t* dist_out, const mlmq_config& c, bool unit_weights,
              bool dev_out, bool* finished);
 // What the host watchdog snapshots when a launch overruns its deadline.
 struct WatchdogView {

@@ -1,0 +1,69 @@
+// Keeping the device a few launches ahead (host side of the stepping and the
+// tiled solve), and the two as one kind of solve in flight.
+#pragma once
+
+#include <hip/hip_runtime.h>
+
+#include <chrono>
+#include <cstdint>
+
+#include "mlmq_api_internal.h"
+#include "mlmq_step.h"
+#include "mlmq_tile.h"
+
+namespace mlmq {
+
+// Launches kept ahead of the last one known to have begun: enough that the
+// device never waits for the host (a launch costs the host 3 us, the shortest
+// one runs 5 us), few enough that those queued past the end cost little (2 us
+// each).
+constexpr uint32_t kAhead = 5;
+
+// One solve in flight on a stream: begin() enqueues its first launches,
+// advance() the next ones as the device gets to them, finish() waits for the
+// stream and delivers the result. One thread at a time; a solve that was begun
+// must be finished.
+class BulkSolve {
+ public:
+  // timed: fill kernel_ms and worker_ms of c.stats_out.
+  int begin(const mlmq_graph* g, uint32_t source, uint32_t* dist_out, const mlmq_config& c, hipStream_t stream,
+            bool unit_weights, bool dev_out, bool timed);
+  // True once nothing is left to launch (the end, the deadline or an error).
+  bool advance();
+  // The solve's status; *finished = false: nothing was decided, the queue
+  // worker must solve.
+  int finish(bool* finished);
+
+ private:
+  hipError_t launch(uint32_t i);
+  int deliver();
+
+  const mlmq_graph* g_ = nullptr;
+  mlmq_config c_{};
+  uint32_t* dist_out_ = nullptr;
+  hipStream_t stream_ = nullptr;
+  bool unit_ = false, dev_out_ = false, late_ = false, no_room_ = false;
+  Slab* slab_ = nullptr;
+  StepArgs step_{};
+  TileArgs tile_{};
+  uint32_t blocks_ = 0, limit_ = 0, issued_ = 0, spins_ = 0, timeout_ms_ = 0;
+  // words of the waiting host, and where a result check may put its flag
+  volatile uint32_t* begun_ = nullptr;
+  uint32_t* state_ = nullptr;
+  char* desc_ = nullptr;
+  uint32_t* final_ = nullptr;  // the labels in the caller's order, on the device
+  hipError_t e_ = hipSuccess;
+  hipEvent_t ev0_ = nullptr, evw_ = nullptr, ev1_ = nullptr;
+  std::chrono::steady_clock::time_point end_{};
+};
+
+// Parts of the two solves.
+size_t step_memory(const mlmq_graph* g, bool own_lab, bool own_out);
+uint32_t step_arguments(const mlmq_graph* g, char* base, uint32_t source, uint32_t* dist_out, bool dev_out, bool unit,
+                        bool stats, StepArgs* a);  // workgroups of a launch
+size_t tile_memory(const mlmq_graph* g, bool own_out);
+uint32_t tile_arguments(const mlmq_graph* g, char* base, uint32_t source, uint32_t* dist_out, bool dev_out, bool unit,
+                        bool stats, TileArgs* a);
+hipError_t launch_tiles(const TileArgs& a, uint32_t round, uint32_t blocks, hipStream_t s);
+
+}  // namespace mlmq

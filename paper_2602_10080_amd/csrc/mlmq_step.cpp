@@ -5,14 +5,12 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
-#include <atomic>
-#include <chrono>
 #include <cmath>
 #include <cstring>
-#include <thread>
 
 #include "../../include/mlmq.h"
 #include "mlmq_api_internal.h"
+#include "mlmq_drive.h"
 #include "mlmq_internal.h"
 #include "mlmq_step.h"
 
@@ -23,11 +21,6 @@ namespace mlmq {
 namespace {
 
 size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
-
-// Launches kept ahead of the last step known to have begun: enough that the
-// device never waits for the host (a launch costs the host 3 us, the shortest
-// step 5 us), few enough that the ones queued past the end cost little.
-constexpr uint32_t kAhead = 5;
 
 uint32_t class_shift(uint32_t max_w) {
   uint32_t bits = 0;
@@ -66,48 +59,6 @@ StepLayout step_layout(const mlmq_graph* g, bool own_lab, bool own_out) {
   l.out = take(own_out ? 4ull * g->n : 0);
   l.bytes = o;
   return l;
-}
-
-// Launches steps until one reports the end (true), the limit is reached or
-// the deadline passes (false, *late); the stream is idle afterwards.
-hipError_t drive(const StepArgs& a, uint32_t blocks, uint32_t limit, uint32_t timeout_ms, hipStream_t stream, bool* done,
-                 bool* late) {
-  using clk = std::chrono::steady_clock;
-  const auto end = clk::now() + std::chrono::milliseconds(timeout_ms);
-  StepHost* const h = a.host;
-  uint32_t issued = 0, spins = 0;
-  *done = *late = false;
-  for (;;) {
-    const uint32_t state = __atomic_load_n(&h->state, __ATOMIC_ACQUIRE);
-    if (state) {
-      *done = state == 1;
-      break;
-    }
-    const uint32_t begun = __atomic_load_n(&h->begun, __ATOMIC_RELAXED);
-    if (begun + 1 >= limit) break;
-    if (issued + 1 < limit && issued < begun + kAhead) {
-      const hipError_t e = launch_step(a, ++issued, blocks, stream);
-      if (e != hipSuccess) return e;
-      continue;
-    }
-    if ((++spins & 1023u) == 0) {
-      if (clk::now() > end) {
-        *late = true;
-        break;
-      }
-      const hipError_t e = hipStreamQuery(stream);
-      if (e == hipSuccess && issued + 1 >= limit) break;  // every step ran
-      if (e != hipSuccess && e != hipErrorNotReady) return e;
-    }
-#if defined(__x86_64__)
-    __builtin_ia32_pause();
-#endif
-  }
-  hipError_t e;
-  while ((e = hipStreamQuery(stream)) == hipErrorNotReady) {
-  }
-  if (e == hipSuccess && !*done && __atomic_load_n(&h->state, __ATOMIC_ACQUIRE) == 1) *done = true;
-  return e;
 }
 
 void graph_args(const mlmq_graph* g, StepArgs* a) {
@@ -209,117 +160,29 @@ hipError_t step_prepare(mlmq_graph* g) {
   return hipSuccess;
 }
 
-int run_step(const mlmq_graph* g, uint32_t source, uint32_t* dist_out, const mlmq_config& c, bool unit_weights,
-             bool dev_out, bool* finished) {
-  hipStream_t stream = reinterpret_cast<hipStream_t>(c.stream);
+size_t step_memory(const mlmq_graph* g, bool own_lab, bool own_out) { return step_layout(g, own_lab, own_out).bytes; }
+
+uint32_t step_arguments(const mlmq_graph* g, char* base, uint32_t source, uint32_t* dist_out, bool dev_out, bool unit,
+                        bool stats, StepArgs* a) {
   const bool ordered = g->d_ord_of != nullptr;
   const StepLayout l = step_layout(g, ordered || !dev_out, ordered && !dev_out);
-  *finished = true;
-  Slab* slab = nullptr;
-  const size_t desc_off = l.bytes;
-  const size_t flag_off = align_up(desc_off + sizeof(QueryDesc), 256);
-  int rc = slab_acquire(flag_off + 256, sizeof(StepHost) + sizeof(QueryDesc) + 64, &slab);
-  if (rc == MLMQ_ERR_OUT_OF_MEMORY) {
-    *finished = false;  // the queues may need less
-    return MLMQ_OK;
-  }
-  if (rc) return rc;
-  char* const base = static_cast<char*>(slab->dev);
-  StepHost* const host = static_cast<StepHost*>(slab->host);
-  std::memset(host, 0, sizeof(*host));
-  StepArgs a;
-  std::memset(&a, 0, sizeof(a));
-  graph_args(g, &a);
-  uint32_t* const d_final = dev_out ? dist_out : reinterpret_cast<uint32_t*>(base + (ordered ? l.out : l.lab));
-  a.lab = ordered || !dev_out ? reinterpret_cast<uint32_t*>(base + l.lab) : dist_out;
-  a.out = d_final;
-  a.rec = reinterpret_cast<StepRec*>(base + l.rec);
-  a.shard = reinterpret_cast<StepShard*>(base + l.shard);
-  a.stats = c.stats_out ? reinterpret_cast<StepStats*>(base + l.stats) : nullptr;
-  a.list[0] = reinterpret_cast<uint64_t*>(base + l.list0);
-  a.list[1] = reinterpret_cast<uint64_t*>(base + l.list1);
-  a.settled = reinterpret_cast<uint64_t*>(base + l.settled);
-  a.task[0] = reinterpret_cast<uint64_t*>(base + l.task0);
-  a.task[1] = reinterpret_cast<uint64_t*>(base + l.task1);
-  a.host = host;
-  a.source = ordered ? g->h_ord_of[source] : source;
-  a.cap = l.cap;
-  a.task_cap = l.task_cap;
-  a.unit_w = unit_weights ? 1u : 0u;
-  a.want_max = g->overflow_safe || unit_weights ? 0u : 1u;
-  const uint32_t blocks = step_blocks(g);
-  const uint32_t timeout_ms = c.timeout_ms ? c.timeout_ms : 60000;
-  hipEvent_t ev0 = nullptr, evw = nullptr, ev1 = nullptr;
-  hipError_t e = hipSuccess;
-  if (c.stats_out) {
-    e = hipEventCreate(&ev0);
-    if (e == hipSuccess) e = hipEventCreate(&evw);
-    if (e == hipSuccess) e = hipEventCreate(&ev1);
-    if (e == hipSuccess) e = hipEventRecord(ev0, stream);
-  }
-  if (e == hipSuccess) e = launch_step_init(a, std::max(64u, blocks), stream);
-  if (e == hipSuccess && evw) e = hipEventRecord(evw, stream);
-  bool done = false, late = false;
-  if (e == hipSuccess) e = drive(a, blocks, kStepMax, timeout_ms, stream, &done, &late);
-  if (e == hipSuccess && ev1) e = hipEventRecord(ev1, stream);
-  float ms = 0, wms = 0;
-  if (e == hipSuccess && ev1) e = hipEventSynchronize(ev1);
-  if (e == hipSuccess && ev1) e = hipEventElapsedTime(&ms, ev0, ev1);
-  if (e == hipSuccess && ev1) e = hipEventElapsedTime(&wms, evw, ev1);
-  if (ev0) (void)hipEventDestroy(ev0);
-  if (evw) (void)hipEventDestroy(evw);
-  if (ev1) (void)hipEventDestroy(ev1);
-  if (e != hipSuccess) {
-    slab_release(slab);
-    return hip_fail(e, "stepping solve");
-  }
-  if (!done) {
-    slab_release(slab);
-    if (late) return set_error(MLMQ_ERR_TIMEOUT, "the solve overran its timeout of %u ms", timeout_ms);
-    *finished = false;  // too deep or a list ran over: the queue worker takes it
-    return MLMQ_OK;
-  }
-  if (a.want_max && (uint64_t)host->max_label + g->max_w >= kInf) {
-    // Some candidate may have been too large to store: exact test, an edge
-    // from a finite label to an unreachable one.
-    QueryDesc* h_desc = reinterpret_cast<QueryDesc*>(host + 1);
-    uint32_t* h_flag = reinterpret_cast<uint32_t*>(h_desc + 1);
-    std::memset(h_desc, 0, sizeof(*h_desc));
-    h_desc->off = a.off;
-    h_desc->adj = a.adj;
-    h_desc->dist = a.lab;
-    h_desc->n = a.n;
-    QueryDesc* d_desc = reinterpret_cast<QueryDesc*>(base + desc_off);
-    uint32_t* d_flag = reinterpret_cast<uint32_t*>(base + flag_off);
-    *h_flag = 0;
-    e = hipMemcpyAsync(d_desc, h_desc, sizeof(QueryDesc), hipMemcpyHostToDevice, stream);
-    if (e == hipSuccess) e = hipMemcpyAsync(d_flag, h_flag, 4, hipMemcpyHostToDevice, stream);
-    if (e == hipSuccess) e = launch_overflow_check(d_desc, d_flag, stream);
-    if (e == hipSuccess) e = hipMemcpyAsync(h_flag, d_flag, 4, hipMemcpyDeviceToHost, stream);
-    if (e == hipSuccess) e = hipStreamSynchronize(stream);
-    if (e != hipSuccess) {
-      slab_release(slab);
-      return hip_fail(e, "overflow check");
-    }
-    if (*h_flag) rc = set_error(MLMQ_ERR_DISTANCE_OVERFLOW, "a reachable distance does not fit below 2^32-1");
-  }
-  if (!dev_out) {
-    e = hipMemcpyAsync(dist_out, d_final, 4ull * g->n, hipMemcpyDeviceToHost, stream);
-    if (e == hipSuccess) e = hipStreamSynchronize(stream);
-    if (e != hipSuccess) rc = hip_fail(e, "copying distances");
-  }
-  if (c.stats_out) {
-    QueryCtrl t;
-    std::memset(&t, 0, sizeof(t));
-    t.stats[kCtExpansions] = host->stats[0];
-    t.stats[kCtStale] = host->stats[1];
-    t.stats[kCtEdges] = host->stats[2];
-    t.stats[kCtPushes] = host->stats[3];
-    t.stats[kCtAtomics] = host->stats[4];
-    fill_stats(c.stats_out, t, ms, wms, blocks * kStepWaves, 0);
-  }
-  slab_release(slab);
-  return rc;
+  graph_args(g, a);
+  a->lab = ordered || !dev_out ? reinterpret_cast<uint32_t*>(base + l.lab) : dist_out;
+  a->out = dev_out ? dist_out : reinterpret_cast<uint32_t*>(base + (ordered ? l.out : l.lab));
+  a->rec = reinterpret_cast<StepRec*>(base + l.rec);
+  a->shard = reinterpret_cast<StepShard*>(base + l.shard);
+  a->stats = stats ? reinterpret_cast<StepStats*>(base + l.stats) : nullptr;
+  a->list[0] = reinterpret_cast<uint64_t*>(base + l.list0);
+  a->list[1] = reinterpret_cast<uint64_t*>(base + l.list1);
+  a->settled = reinterpret_cast<uint64_t*>(base + l.settled);
+  a->task[0] = reinterpret_cast<uint64_t*>(base + l.task0);
+  a->task[1] = reinterpret_cast<uint64_t*>(base + l.task1);
+  a->source = ordered ? g->h_ord_of[source] : source;
+  a->cap = l.cap;
+  a->task_cap = l.task_cap;
+  a->unit_w = unit ? 1u : 0u;
+  a->want_max = g->overflow_safe || unit ? 0u : 1u;
+  return step_blocks(g);
 }
 
 }  // namespace mlmq
