@@ -1,4 +1,6 @@
-// Batched solves in one persistent, hipGraph-captured launch.
+// Batched solves: queries that run as sequences of launches (stepping, tiled),
+// several at once on streams of their own; the others in one persistent,
+// hipGraph-captured launch.
 
 #include <hip/hip_runtime.h>
 
@@ -40,26 +42,25 @@ bool device_ptr(const void* p) {
 
 }  // namespace
 
-extern "C" int mlmq_sssp_batch(const mlmq_graph* const* graphs, const uint32_t* sources, uint32_t* const* dist_outs,
-                               int32_t nq, const mlmq_config* const* cfgs, int32_t* per_query_status) {
-  if (nq < 1 || !graphs || !sources || !dist_outs) return set_error(MLMQ_ERR_INVALID_ARG, "empty or NULL batch");
-  int rc = need_device();
-  if (rc) return rc;
+// Queries `which` in one persistent launch of the queue worker, with the
+// launch shape and stream of lc; status[i] for each of them.
+static int queue_batch(const mlmq_graph* const* all_graphs, const uint32_t* all_sources, uint32_t* const* all_outs,
+                       const std::vector<mlmq_config>& all_conf, const mlmq_config* const* all_cfgs,
+                       const std::vector<int32_t>& which, mlmq_config lc, int32_t* all_status) {
+  const int32_t nq = (int32_t)which.size();
+  std::vector<const mlmq_graph*> graphs((size_t)nq);
+  std::vector<uint32_t> sources((size_t)nq);
+  std::vector<uint32_t*> dist_outs((size_t)nq);
   std::vector<mlmq_config> conf((size_t)nq);
   for (int32_t i = 0; i < nq; ++i) {
-    if (!graphs[i]) return set_error(MLMQ_ERR_INVALID_ARG, "graphs[%d] is NULL", i);
-    if (sources[i] >= (uint32_t)graphs[i]->n)
-      return set_error(MLMQ_ERR_INVALID_ARG, "sources[%d] = %u out of range", i, sources[i]);
-    if (!dist_outs[i] || !device_ptr(dist_outs[i]))
-      return set_error(MLMQ_ERR_INVALID_ARG, "dist_outs[%d] must be device memory", i);
-    mlmq_config tmp;
-    conf[i] = *resolve_config(graphs[i], cfgs ? cfgs[i] : nullptr, &tmp);
-    rc = check_config(&conf[i]);
-    if (rc) return rc;
+    graphs[i] = all_graphs[which[i]];
+    sources[i] = all_sources[which[i]];
+    dist_outs[i] = all_outs[which[i]];
+    conf[i] = all_conf[which[i]];
   }
+  int rc = MLMQ_OK;
   // Launch shape from the first config, but always the whole device: the
   // queries share it. LDS is sized for the largest L1.
-  mlmq_config lc = conf[0];
   lc.grid_wgs = 0;
   uint32_t l1cap = 64;
   bool two = false, stage = false, pq = false;
@@ -165,7 +166,6 @@ extern "C" int mlmq_sssp_batch(const mlmq_graph* const* graphs, const uint32_t* 
     slab_release(slab);
     return hip_fail(e, "batch launch");
   }
-  int first_bad = MLMQ_OK;
   std::vector<int32_t> status((size_t)nq, MLMQ_OK);
   std::vector<int32_t> redo;
   for (int32_t k = 0; k < nq; ++k) {
@@ -177,12 +177,12 @@ extern "C" int mlmq_sssp_batch(const mlmq_graph* const* graphs, const uint32_t* 
     }
     if (st == MLMQ_OK && h_res[k].overflow && !graphs[i]->overflow_safe) redo.push_back(i);
     status[i] = st;
-    if (cfgs && cfgs[i] && cfgs[i]->stats_out) {
+    if (all_cfgs && all_cfgs[which[i]] && all_cfgs[which[i]]->stats_out) {
       QueryCtrl tmp;
       std::memset(&tmp, 0, sizeof(tmp));
       tmp.error.v = h_res[k].error;
       for (int j = 0; j < kNumCounters; ++j) tmp.stats[j] = h_res[k].stats[j];
-      fill_stats(cfgs[i]->stats_out, tmp, 0.0, 0.0, h_desc[k].want_wgs, 0);
+      fill_stats(all_cfgs[which[i]]->stats_out, tmp, 0.0, 0.0, h_desc[k].want_wgs, 0);
     }
   }
   slab_release(slab);
@@ -191,6 +191,43 @@ extern "C" int mlmq_sssp_batch(const mlmq_graph* const* graphs, const uint32_t* 
     c.stream = reinterpret_cast<void*>(stream);
     status[i] = run_single(graphs[i], sources[i], dist_outs[i], c);
   }
+  for (int32_t i = 0; i < nq; ++i) all_status[which[i]] = status[i];
+  return MLMQ_OK;
+}
+
+extern "C" int mlmq_sssp_batch(const mlmq_graph* const* graphs, const uint32_t* sources, uint32_t* const* dist_outs,
+                               int32_t nq, const mlmq_config* const* cfgs, int32_t* per_query_status) {
+  if (nq < 1 || !graphs || !sources || !dist_outs) return set_error(MLMQ_ERR_INVALID_ARG, "empty or NULL batch");
+  int rc = need_device();
+  if (rc) return rc;
+  std::vector<mlmq_config> conf((size_t)nq);
+  std::vector<int32_t> bulk, queues;
+  for (int32_t i = 0; i < nq; ++i) {
+    if (!graphs[i]) return set_error(MLMQ_ERR_INVALID_ARG, "graphs[%d] is NULL", i);
+    if (sources[i] >= (uint32_t)graphs[i]->n)
+      return set_error(MLMQ_ERR_INVALID_ARG, "sources[%d] = %u out of range", i, sources[i]);
+    if (!dist_outs[i] || !device_ptr(dist_outs[i]))
+      return set_error(MLMQ_ERR_INVALID_ARG, "dist_outs[%d] must be device memory", i);
+    mlmq_config tmp;
+    conf[i] = *resolve_config(graphs[i], cfgs ? cfgs[i] : nullptr, &tmp);
+    rc = check_config(&conf[i]);
+    if (rc) return rc;
+    (bulk_solves(graphs[i], conf[i], false) ? bulk : queues).push_back(i);
+  }
+  const mlmq_config lc = conf[0];
+  std::vector<int32_t> status((size_t)nq, MLMQ_OK);
+  if (!bulk.empty()) {
+    // largest first, so the long ones start early
+    std::stable_sort(bulk.begin(), bulk.end(), [&](int32_t a, int32_t b) { return graphs[a]->m > graphs[b]->m; });
+    rc = run_bulk_batch(graphs, sources, dist_outs, conf.data(), bulk, reinterpret_cast<hipStream_t>(lc.stream),
+                        lc.timeout_ms, status.data(), &queues);
+    if (rc) return rc;
+  }
+  if (!queues.empty()) {
+    rc = queue_batch(graphs, sources, dist_outs, conf, cfgs, queues, lc, status.data());
+    if (rc) return rc;
+  }
+  int first_bad = MLMQ_OK;
   for (int32_t i = 0; i < nq; ++i) {
     if (per_query_status) per_query_status[i] = status[i];
     if (status[i] != MLMQ_OK && first_bad == MLMQ_OK) first_bad = status[i];

@@ -1,9 +1,12 @@
-// Solves that run as a sequence of launches (stepping and tiled).
+// Solves that run as a sequence of launches (stepping and tiled), alone or
+// several at once.
 
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
 #include <cstring>
+#include <mutex>
+#include <vector>
 
 #include "../../include/mlmq.h"
 #include "mlmq_api_internal.h"
@@ -17,6 +20,52 @@ namespace mlmq {
 namespace {
 
 size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
+
+// Solves in flight at once in a batch: one hardware queue each.
+constexpr int kLanes = 4;
+
+// Streams of one batch at a time; a few sets are kept for the next ones.
+struct Streams {
+  hipStream_t s[kLanes] = {};
+};
+std::mutex g_streams_mu;
+std::vector<Streams*> g_streams;
+constexpr size_t kKeptSets = 4;
+
+hipError_t streams_acquire(Streams** out) {
+  {
+    std::lock_guard<std::mutex> lk(g_streams_mu);
+    if (!g_streams.empty()) {
+      *out = g_streams.back();
+      g_streams.pop_back();
+      return hipSuccess;
+    }
+  }
+  Streams* t = new Streams();
+  hipError_t e = hipSuccess;
+  for (hipStream_t& s : t->s)
+    if (e == hipSuccess) e = hipStreamCreateWithFlags(&s, hipStreamNonBlocking);
+  if (e != hipSuccess) {
+    for (hipStream_t s : t->s)
+      if (s) (void)hipStreamDestroy(s);
+    delete t;
+    return e;
+  }
+  *out = t;
+  return hipSuccess;
+}
+
+void streams_release(Streams* t) {
+  {
+    std::lock_guard<std::mutex> lk(g_streams_mu);
+    if (g_streams.size() < kKeptSets) {
+      g_streams.push_back(t);
+      return;
+    }
+  }
+  for (hipStream_t s : t->s) (void)hipStreamDestroy(s);
+  delete t;
+}
 
 }  // namespace
 
@@ -183,6 +232,57 @@ int run_bulk(const mlmq_graph* g, uint32_t source, uint32_t* dist_out, const mlm
   if (rc) return rc;
   while (!s.advance()) __builtin_ia32_pause();
   return s.finish(finished);
+}
+
+// Queries `which` of a batch, kLanes at a time on streams of their own, which
+// start after what `after` (if given) holds so far. Those that nothing was decided for
+// come back in *left.
+int run_bulk_batch(const mlmq_graph* const* graphs, const uint32_t* sources, uint32_t* const* dist_outs,
+                   const mlmq_config* conf, const std::vector<int32_t>& which, hipStream_t after,
+                   uint32_t timeout_ms, int32_t* status, std::vector<int32_t>* left) {
+  Streams* streams = nullptr;
+  hipError_t e = streams_acquire(&streams);
+  if (e != hipSuccess) return hip_fail(e, "batch streams");
+  if (after) {
+    hipEvent_t ev = nullptr;
+    e = hipEventCreateWithFlags(&ev, hipEventDisableTiming);
+    if (e == hipSuccess) e = hipEventRecord(ev, after);
+    for (hipStream_t s : streams->s)
+      if (e == hipSuccess) e = hipStreamWaitEvent(s, ev, 0);
+    if (ev) (void)hipEventDestroy(ev);
+    if (e != hipSuccess) {
+      streams_release(streams);
+      return hip_fail(e, "batch streams");
+    }
+  }
+  BulkSolve lane[kLanes];
+  int32_t query[kLanes];
+  size_t next = 0;
+  int busy = 0;
+  for (int32_t& q : query) q = -1;
+  do {
+    for (int k = 0; k < kLanes; ++k) {
+      if (query[k] < 0 && next < which.size()) {
+        const int32_t i = which[next++];
+        mlmq_config c = conf[i];
+        c.timeout_ms = timeout_ms;
+        status[i] = lane[k].begin(graphs[i], sources[i], dist_outs[i], c, streams->s[k], false, true, false);
+        if (status[i] == MLMQ_OK) {
+          query[k] = i;
+          ++busy;
+        }
+      }
+      if (query[k] >= 0 && lane[k].advance()) {
+        bool finished = true;
+        status[query[k]] = lane[k].finish(&finished);
+        if (!finished) left->push_back(query[k]);
+        query[k] = -1;
+        --busy;
+      }
+    }
+  } while (busy || next < which.size());
+  streams_release(streams);
+  return MLMQ_OK;
 }
 
 }  // namespace mlmq
