@@ -1,5 +1,5 @@
 // Batched solves: queries that run as sequences of launches (stepping, tiled),
-// several at once on streams of their own; the others in one persistent,
+// several in the same launches; the others in one persistent,
 // hipGraph-captured launch.
 
 #include <hip/hip_runtime.h>

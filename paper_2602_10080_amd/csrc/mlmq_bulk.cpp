@@ -1,5 +1,5 @@
 // Solves that run as a sequence of launches (stepping and tiled), alone or
-// several at once.
+// several in the same launches.
 
 #include <hip/hip_runtime.h>
 
@@ -21,8 +21,12 @@ namespace {
 
 size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
-// Solves in flight at once in a batch: one hardware queue each.
-constexpr int kLanes = 4;
+// Groups of solves in flight at once in a batch: stepping ones, tiled ones and
+// tiled ones of graphs that are one tile.
+constexpr int kLanes = 3;
+// Solves that share their launches, and the memory they may take together.
+constexpr size_t kGroup = 32;
+constexpr size_t kGroupBytes = 16ull << 30;
 
 // Streams of one batch at a time; a few sets are kept for the next ones.
 struct Streams {
@@ -73,8 +77,8 @@ hipError_t BulkSolve::launch(uint32_t i) {
   return g_->tiles ? launch_tiles(tile_, i, blocks_, stream_) : launch_step(step_, i, blocks_, stream_);
 }
 
-int BulkSolve::begin(const mlmq_graph* g, uint32_t source, uint32_t* dist_out, const mlmq_config& c, hipStream_t stream,
-                     bool unit_weights, bool dev_out, bool timed) {
+int BulkSolve::prepare(const mlmq_graph* g, uint32_t source, uint32_t* dist_out, const mlmq_config& c,
+                       hipStream_t stream, bool unit_weights, bool dev_out, bool timed) {
   *this = BulkSolve();
   g_ = g;
   c_ = c;
@@ -117,9 +121,14 @@ int BulkSolve::begin(const mlmq_graph* g, uint32_t source, uint32_t* dist_out, c
     if (e_ == hipSuccess) e_ = hipEventCreate(&ev1_);
     if (e_ == hipSuccess) e_ = hipEventRecord(ev0_, stream);
   }
-  if (e_ == hipSuccess) e_ = g->tiles ? launch_tile_init(tile_, stream) : launch_step_init(step_, std::max(64u, blocks_), stream);
-  if (e_ == hipSuccess && evw_) e_ = hipEventRecord(evw_, stream);
   return MLMQ_OK;
+}
+
+void BulkSolve::begin() {
+  if (no_room_) return;
+  if (e_ == hipSuccess)
+    e_ = g_->tiles ? launch_tile_init(tile_, stream_) : launch_step_init(step_, std::max(64u, blocks_), stream_);
+  if (e_ == hipSuccess && evw_) e_ = hipEventRecord(evw_, stream_);
 }
 
 bool BulkSolve::advance() {
@@ -227,19 +236,159 @@ bool bulk_solves(const mlmq_graph* g, const mlmq_config& c, bool unit_weights) {
 int run_bulk(const mlmq_graph* g, uint32_t source, uint32_t* dist_out, const mlmq_config& c, bool unit_weights,
              bool dev_out, bool* finished) {
   BulkSolve s;
-  const int rc = s.begin(g, source, dist_out, c, reinterpret_cast<hipStream_t>(c.stream), unit_weights, dev_out, true);
+  const int rc = s.prepare(g, source, dist_out, c, reinterpret_cast<hipStream_t>(c.stream), unit_weights, dev_out, true);
   *finished = true;
   if (rc) return rc;
+  s.begin();
   while (!s.advance()) __builtin_ia32_pause();
   return s.finish(finished);
 }
 
-// Queries `which` of a batch, kLanes at a time on streams of their own, which
-// start after what `after` (if given) holds so far. Those that nothing was decided for
-// come back in *left.
+namespace {
+
+// Solves of one kind in lockstep: one launch serves all of them, a grid row
+// each, until every one has reported its end.
+class BulkGroup {
+ public:
+  // Takes queries from which[*next] on while they are of one kind and fit.
+  void begin(const mlmq_graph* const* graphs, const uint32_t* sources, uint32_t* const* dist_outs,
+             const mlmq_config* conf, const std::vector<int32_t>& which, size_t* next, hipStream_t stream,
+             uint32_t timeout_ms, int32_t* status, std::vector<int32_t>* left);
+  bool advance();
+  void finish(int32_t* status, std::vector<int32_t>* left);
+  bool busy() const { return !solves_.empty(); }
+
+ private:
+  std::vector<BulkSolve> solves_;
+  std::vector<int32_t> query_;
+  Slab* args_ = nullptr;
+  hipStream_t stream_ = nullptr;
+  bool tiled_ = false, late_ = false;
+  uint32_t blocks_ = 0, limit_ = 0, issued_ = 0, spins_ = 0;
+  hipError_t e_ = hipSuccess;
+  std::chrono::steady_clock::time_point end_{};
+
+  hipError_t launch(uint32_t i) {
+    const uint32_t n = (uint32_t)solves_.size();
+    if (tiled_)
+      return launch_tiles_many(static_cast<const TileArgs*>(args_->dev), solves_[0].tile_args().g, n, i, blocks_, stream_);
+    return launch_step_many(static_cast<const StepArgs*>(args_->dev), n, i, blocks_, stream_);
+  }
+};
+
+void BulkGroup::begin(const mlmq_graph* const* graphs, const uint32_t* sources, uint32_t* const* dist_outs,
+                      const mlmq_config* conf, const std::vector<int32_t>& which, size_t* next, hipStream_t stream,
+                      uint32_t timeout_ms, int32_t* status, std::vector<int32_t>* left) {
+  *this = BulkGroup();
+  stream_ = stream;
+  size_t bytes = 0;
+  uint32_t most = 0, tiles = 0;
+  while (*next < which.size() && solves_.size() < kGroup) {
+    const int32_t i = which[*next];
+    const mlmq_graph* g = graphs[i];
+    const size_t mem = g->tiles ? tile_memory(g, false) : step_memory(g, g->d_ord_of != nullptr, false);
+    if (!solves_.empty() && bytes + mem > kGroupBytes) break;
+    mlmq_config c = conf[i];
+    c.timeout_ms = timeout_ms;
+    BulkSolve s;
+    const int rc = s.prepare(g, sources[i], dist_outs[i], c, stream, false, true, false);
+    if (s.no_room() && !solves_.empty()) break;  // as many as fit now, the others after them
+    ++*next;
+    if (rc) {
+      status[i] = rc;
+      continue;
+    }
+    if (s.no_room()) {
+      left->push_back(i);
+      continue;
+    }
+    bytes += mem;
+    tiled_ = g->tiles != nullptr;
+    most = std::max(most, s.blocks());
+    if (tiled_) tiles = std::max(tiles, tile_count(g));
+    solves_.push_back(s);
+    query_.push_back(i);
+  }
+  if (solves_.empty()) return;
+  // The rows share the device. Stepping solves fill it by themselves in their
+  // large steps, and a wave pays for itself in the list counters it reads (16
+  // sources on RMAT-20: two / four / eight launches' worth of workgroups 5.9 /
+  // 4.6 / 4.3 ms); a tiled round has tiles for one launch's worth (8 sources on
+  // a 1024 x 1024 grid: one / two / four 10.4 / 10.2 / 11.5 ms, 32 sources 18.7 /
+  // 19.1 / 20.0).
+  const uint32_t n = (uint32_t)solves_.size();
+  const uint32_t all = (tiled_ ? 1u : 8u) * most;
+  blocks_ = std::min(most, std::max((all + n - 1u) / n, most / 16u + 1u));
+  if (tiled_) blocks_ = std::max(blocks_, (tiles + kTileVisits - 1u) / kTileVisits);
+  limit_ = tiled_ ? kTileRounds : kStepMax;
+  end_ = std::chrono::steady_clock::now() + std::chrono::milliseconds(timeout_ms ? timeout_ms : 60000);
+  const size_t one = tiled_ ? sizeof(TileArgs) : sizeof(StepArgs);
+  if (slab_acquire(one * n, one * n, &args_) != MLMQ_OK) {
+    e_ = hipErrorOutOfMemory;  // finish() reports it
+    return;
+  }
+  for (uint32_t i = 0; i < n; ++i) {
+    char* to = static_cast<char*>(args_->host) + one * i;
+    if (tiled_)
+      std::memcpy(to, &solves_[i].tile_args(), one);
+    else
+      std::memcpy(to, &solves_[i].step_args(), one);
+  }
+  e_ = hipMemcpyAsync(args_->dev, args_->host, one * n, hipMemcpyHostToDevice, stream);
+  if (e_ == hipSuccess) e_ = launch(0);
+}
+
+bool BulkGroup::advance() {
+  for (;;) {
+    if (e_ != hipSuccess) return true;
+    bool over = true;
+    uint32_t begun = 0;  // all rows of a launch begin together
+    for (const BulkSolve& s : solves_) {
+      over = over && s.over();
+      begun = std::max(begun, s.begun());
+    }
+    if (over) return true;
+    if (issued_ + 1 < limit_ && issued_ < begun + kAhead) {
+      e_ = launch(++issued_);
+      continue;
+    }
+    if ((++spins_ & 1023u) == 0) {
+      if (std::chrono::steady_clock::now() > end_) {
+        late_ = true;
+        return true;
+      }
+      const hipError_t q = hipStreamQuery(stream_);
+      if (q == hipSuccess && issued_ + 1 >= limit_) return true;
+      if (q != hipSuccess && q != hipErrorNotReady) e_ = q;
+    }
+    return e_ != hipSuccess;
+  }
+}
+
+void BulkGroup::finish(int32_t* status, std::vector<int32_t>* left) {
+  for (size_t i = 0; i < solves_.size(); ++i) {
+    if (e_ != hipSuccess) solves_[i].fail(e_);
+    if (late_) solves_[i].set_late();
+    bool finished = true;
+    status[query_[i]] = solves_[i].finish(&finished);  // waits for the stream
+    if (!finished) left->push_back(query_[i]);
+  }
+  solves_.clear();
+  slab_release(args_);
+  args_ = nullptr;
+}
+
+}  // namespace
+
+// Queries `which` of a batch in groups that share their launches, on streams of
+// their own, which start after what `after` (if given) holds so far. Those that
+// nothing was decided for come back in *left.
 int run_bulk_batch(const mlmq_graph* const* graphs, const uint32_t* sources, uint32_t* const* dist_outs,
                    const mlmq_config* conf, const std::vector<int32_t>& which, hipStream_t after,
                    uint32_t timeout_ms, int32_t* status, std::vector<int32_t>* left) {
+  std::vector<int32_t> of[kLanes];
+  for (int32_t i : which)
+    of[!graphs[i]->tiles ? 0 : (tile_kind(graphs[i]) < kTileLocalBits ? 1 : 2)].push_back(i);
   Streams* streams = nullptr;
   hipError_t e = streams_acquire(&streams);
   if (e != hipSuccess) return hip_fail(e, "batch streams");
@@ -255,32 +404,17 @@ int run_bulk_batch(const mlmq_graph* const* graphs, const uint32_t* sources, uin
       return hip_fail(e, "batch streams");
     }
   }
-  BulkSolve lane[kLanes];
-  int32_t query[kLanes];
-  size_t next = 0;
-  int busy = 0;
-  for (int32_t& q : query) q = -1;
-  do {
+  BulkGroup group[kLanes];
+  size_t next[kLanes] = {};
+  for (bool more = true; more;) {
+    more = false;
     for (int k = 0; k < kLanes; ++k) {
-      if (query[k] < 0 && next < which.size()) {
-        const int32_t i = which[next++];
-        mlmq_config c = conf[i];
-        c.timeout_ms = timeout_ms;
-        status[i] = lane[k].begin(graphs[i], sources[i], dist_outs[i], c, streams->s[k], false, true, false);
-        if (status[i] == MLMQ_OK) {
-          query[k] = i;
-          ++busy;
-        }
-      }
-      if (query[k] >= 0 && lane[k].advance()) {
-        bool finished = true;
-        status[query[k]] = lane[k].finish(&finished);
-        if (!finished) left->push_back(query[k]);
-        query[k] = -1;
-        --busy;
-      }
+      if (!group[k].busy() && next[k] < of[k].size())
+        group[k].begin(graphs, sources, dist_outs, conf, of[k], &next[k], streams->s[k], timeout_ms, status, left);
+      if (group[k].busy() && group[k].advance()) group[k].finish(status, left);
+      more = more || group[k].busy() || next[k] < of[k].size();
     }
-  } while (busy || next < which.size());
+  }
   streams_release(streams);
   return MLMQ_OK;
 }

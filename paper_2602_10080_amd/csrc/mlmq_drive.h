@@ -19,20 +19,31 @@ namespace mlmq {
 // each).
 constexpr uint32_t kAhead = 5;
 
-// One solve in flight on a stream: begin() enqueues its first launches,
-// advance() the next ones as the device gets to them, finish() waits for the
-// stream and delivers the result. One thread at a time; a solve that was begun
-// must be finished.
+// One solve on a stream: prepare() takes its memory and lays out its
+// arguments, begin() enqueues its first launch, advance() the next ones as the
+// device gets to them, finish() waits for the stream and delivers the result.
+// One thread at a time; a solve that was prepared must be finished.
 class BulkSolve {
  public:
   // timed: fill kernel_ms and worker_ms of c.stats_out.
-  int begin(const mlmq_graph* g, uint32_t source, uint32_t* dist_out, const mlmq_config& c, hipStream_t stream,
-            bool unit_weights, bool dev_out, bool timed);
+  int prepare(const mlmq_graph* g, uint32_t source, uint32_t* dist_out, const mlmq_config& c, hipStream_t stream,
+                bool unit_weights, bool dev_out, bool timed);
+  void begin();
   // True once nothing is left to launch (the end, the deadline or an error).
   bool advance();
   // The solve's status; *finished = false: nothing was decided, the queue
   // worker must solve.
   int finish(bool* finished);
+
+  bool no_room() const { return no_room_; }
+  // For solves that share their launches: what a launch needs and tells.
+  const StepArgs& step_args() const { return step_; }
+  const TileArgs& tile_args() const { return tile_; }
+  uint32_t blocks() const { return blocks_; }
+  bool over() const { return __atomic_load_n(state_, __ATOMIC_ACQUIRE) != 0; }
+  uint32_t begun() const { return *begun_; }
+  void fail(hipError_t e) { e_ = e; }
+  void set_late() { late_ = true; }
 
  private:
   hipError_t launch(uint32_t i);
@@ -65,5 +76,9 @@ size_t tile_memory(const mlmq_graph* g, bool own_out);
 uint32_t tile_arguments(const mlmq_graph* g, char* base, uint32_t source, uint32_t* dist_out, bool dev_out, bool unit,
                         bool stats, TileArgs* a);
 hipError_t launch_tiles(const TileArgs& a, uint32_t round, uint32_t blocks, hipStream_t s);
+hipError_t launch_tiles_many(const TileArgs* d_args, const TileGraph& like, uint32_t count, uint32_t round,
+                             uint32_t blocks, hipStream_t s);
+uint32_t tile_kind(const mlmq_graph* g);   // graphs of one kind share a launch
+uint32_t tile_count(const mlmq_graph* g);
 
 }  // namespace mlmq

@@ -112,6 +112,8 @@ struct StepArgs {
 // Kernel launchers.
 hipError_t launch_step_init(const StepArgs& a, uint32_t blocks, hipStream_t s);
 hipError_t launch_step(const StepArgs& a, uint32_t step, uint32_t blocks, hipStream_t s);
+// One step of `count` solves (arguments in device memory); step 0 is the reset.
+hipError_t launch_step_many(const StepArgs* d_args, uint32_t count, uint32_t step, uint32_t blocks, hipStream_t s);
 
 // Rows in ascending weight class: adj_out may not be adj_in. Rows keep their bounds.
 hipError_t launch_sort_rows(const int32_t* off, const uint64_t* adj_in, uint64_t* adj_out, uint32_t n, uint32_t shift,

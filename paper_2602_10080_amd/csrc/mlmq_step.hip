@@ -780,7 +780,7 @@ constexpr uint32_t kStepHeadLds = 8u + 3u * kStepWaves + kStepWaves;
 constexpr uint32_t kStepWaveLds = 2u * 128u + 32u;
 constexpr uint32_t kStepLds = 8u * (kStepHeadLds + kStepWaves * kStepWaveLds);
 
-__global__ void __launch_bounds__(64 * kStepWaves) mlmq_step(StepArgs a, uint32_t step) {
+__device__ __forceinline__ void step_body(const StepArgs& a, uint32_t step) {
   extern __shared__ uint64_t smem[];
   uint32_t* const dec = reinterpret_cast<uint32_t*>(smem);
   ScanSum* const sums = reinterpret_cast<ScanSum*>(smem + 8);
@@ -856,9 +856,16 @@ __global__ void __launch_bounds__(64 * kStepWaves) mlmq_step(StepArgs a, uint32_
   }
 }
 
+__global__ void __launch_bounds__(64 * kStepWaves) mlmq_step(StepArgs a, uint32_t step) { step_body(a, step); }
+// The same step of several solves, one a grid row: the launches and the steps
+// with little to do are shared.
+__global__ void __launch_bounds__(64 * kStepWaves) mlmq_step_many(const StepArgs* all, uint32_t step) {
+  step_body(all[blockIdx.y], step);
+}
+
 // Step 0: labels unreachable but the source's, counters zero, the source in
 // the first list, thresholds of the first distance step.
-__global__ void __launch_bounds__(256) mlmq_step_init(StepArgs a) {
+__device__ __forceinline__ void step_init_body(const StepArgs& a) {
   const uint32_t tid = blockIdx.x * blockDim.x + threadIdx.x, stride = gridDim.x * blockDim.x;
   for (uint64_t i = tid; i < a.n; i += stride) a.lab[i] = i == a.source ? 0u : kInf32;
   uint32_t* const rec = reinterpret_cast<uint32_t*>(a.rec);
@@ -890,6 +897,9 @@ __global__ void __launch_bounds__(256) mlmq_step_init(StepArgs a) {
   }
   if (tid == 0u) a.list[0][0] = make_elem(a.source, 0u);
 }
+
+__global__ void __launch_bounds__(256) mlmq_step_init(StepArgs a) { step_init_body(a); }
+__global__ void __launch_bounds__(256) mlmq_step_init_many(const StepArgs* all) { step_init_body(all[blockIdx.y]); }
 
 // ------------------------------------------------------------ graph preparation
 
@@ -1047,6 +1057,14 @@ hipError_t launch_step_init(const StepArgs& a, uint32_t blocks, hipStream_t s) {
 
 hipError_t launch_step(const StepArgs& a, uint32_t step, uint32_t blocks, hipStream_t s) {
   hipLaunchKernelGGL(mlmq_step, dim3(blocks), dim3(64 * kStepWaves), kStepLds, s, a, step);
+  return hipGetLastError();
+}
+
+hipError_t launch_step_many(const StepArgs* d_args, uint32_t count, uint32_t step, uint32_t blocks, hipStream_t s) {
+  if (step == 0u)
+    hipLaunchKernelGGL(mlmq_step_init_many, dim3(blocks < 64u ? 64u : blocks, count), dim3(256), 0, s, d_args);
+  else
+    hipLaunchKernelGGL(mlmq_step_many, dim3(blocks, count), dim3(64 * kStepWaves), kStepLds, s, d_args, step);
   return hipGetLastError();
 }
 

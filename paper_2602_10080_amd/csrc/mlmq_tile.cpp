@@ -262,4 +262,12 @@ hipError_t launch_tiles(const TileArgs& a, uint32_t round, uint32_t blocks, hipS
   return launch_tile_round(a, round, blocks, kThreads, s);
 }
 
+hipError_t launch_tiles_many(const TileArgs* d_args, const TileGraph& like, uint32_t count, uint32_t round,
+                             uint32_t blocks, hipStream_t s) {
+  return launch_tile_many(d_args, count, round, blocks, kThreads, tile_lds_bytes(like.sbits, like.xcap, kThreads), s);
+}
+
+uint32_t tile_kind(const mlmq_graph* g) { return g->tiles->g.sbits; }
+uint32_t tile_count(const mlmq_graph* g) { return g->tiles->g.tiles; }
+
 }  // namespace mlmq

@@ -72,6 +72,10 @@ struct TileArgs {
 size_t tile_lds_bytes(uint32_t sbits, uint32_t xcap, uint32_t threads);
 hipError_t launch_tile_init(const TileArgs& a, hipStream_t s);
 hipError_t launch_tile_round(const TileArgs& a, uint32_t round, uint32_t blocks, uint32_t threads, hipStream_t s);
+// One round of `count` solves (arguments in device memory); round 0 is the reset.
+hipError_t launch_tile_many(const TileArgs* d_args, uint32_t count, uint32_t round, uint32_t blocks, uint32_t threads,
+                            size_t lds, hipStream_t s);
+// Dynamic LDS that the round kernels may use.
 hipError_t tile_set_lds(size_t bytes);
 
 // Building the tiled copy. inv: [tiles << sbits] caller's vertex of an id (kInf: none).

@@ -294,7 +294,7 @@ __device__ __forceinline__ void add_work(uint64_t* to, uint32_t mine) {
 
 // One round: the tiles with a label pending below the limit, or, when nothing
 // is pending, the labels in the caller's order, then the report to the host.
-__global__ void __launch_bounds__(1024) mlmq_tile_round(TileArgs a, uint32_t round) {
+__device__ __forceinline__ void tile_round_body(const TileArgs& a, uint32_t round) {
   extern __shared__ uint64_t smem[];
   const Lds l = carve(smem, a.g.sbits, a.g.xcap);
   const uint32_t tid = threadIdx.x, nt = blockDim.x;
@@ -405,8 +405,14 @@ __global__ void __launch_bounds__(1024) mlmq_tile_round(TileArgs a, uint32_t rou
   }
 }
 
+__global__ void __launch_bounds__(1024) mlmq_tile_round(TileArgs a, uint32_t round) { tile_round_body(a, round); }
+// The same round of several solves, one a grid row.
+__global__ void __launch_bounds__(1024) mlmq_tile_round_many(const TileArgs* all, uint32_t round) {
+  tile_round_body(all[blockIdx.y], round);
+}
+
 // Round 0: labels unreachable and nothing expanded, the source pending at 0.
-__global__ void __launch_bounds__(256) mlmq_tile_init(TileArgs a) {
+__device__ __forceinline__ void tile_init_body(const TileArgs& a) {
   const uint64_t tid = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x, stride = (uint64_t)gridDim.x * blockDim.x;
   const uint64_t ids = (uint64_t)a.g.tiles << a.g.sbits;
   for (uint64_t i = tid; i < ids; i += stride) {
@@ -424,6 +430,9 @@ __global__ void __launch_bounds__(256) mlmq_tile_init(TileArgs a) {
     s->inv_max = kInf32;
   }
 }
+
+__global__ void __launch_bounds__(256) mlmq_tile_init(TileArgs a) { tile_init_body(a); }
+__global__ void __launch_bounds__(256) mlmq_tile_init_many(const TileArgs* all) { tile_init_body(all[blockIdx.y]); }
 
 // ------------------------------------------------------------ building the tiled copy
 
@@ -515,8 +524,12 @@ size_t tile_lds_bytes(uint32_t sbits, uint32_t xcap, uint32_t threads) {
 }
 
 hipError_t tile_set_lds(size_t bytes) {
-  return hipFuncSetAttribute(reinterpret_cast<const void*>(mlmq_tile_round), hipFuncAttributeMaxDynamicSharedMemorySize,
-                             (int)bytes);
+  hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(mlmq_tile_round),
+                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
+  if (e == hipSuccess)
+    e = hipFuncSetAttribute(reinterpret_cast<const void*>(mlmq_tile_round_many),
+                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
+  return e;
 }
 
 hipError_t launch_tile_init(const TileArgs& a, hipStream_t s) {
@@ -527,6 +540,15 @@ hipError_t launch_tile_init(const TileArgs& a, hipStream_t s) {
 
 hipError_t launch_tile_round(const TileArgs& a, uint32_t round, uint32_t blocks, uint32_t threads, hipStream_t s) {
   hipLaunchKernelGGL(mlmq_tile_round, dim3(blocks), dim3(threads), tile_lds_bytes(a.g.sbits, a.g.xcap, threads), s, a, round);
+  return hipGetLastError();
+}
+
+hipError_t launch_tile_many(const TileArgs* d_args, uint32_t count, uint32_t round, uint32_t blocks, uint32_t threads,
+                            size_t lds, hipStream_t s) {
+  if (round == 0u)
+    hipLaunchKernelGGL(mlmq_tile_init_many, dim3(256, count), dim3(256), 0, s, d_args);
+  else
+    hipLaunchKernelGGL(mlmq_tile_round_many, dim3(blocks, count), dim3(threads), lds, s, d_args, round);
   return hipGetLastError();
 }
 
