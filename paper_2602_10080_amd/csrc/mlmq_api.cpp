@@ -235,12 +235,13 @@ void free_graph_arrays(mlmq_graph* g) {
   (void)hipFree(g->d_off_ord);
   (void)hipFree(g->d_adj_ord);
   (void)hipFree(g->d_ord_of);
+  (void)hipFree(g->d_sadj);
   (void)hipFree(g->d_ioff);
   (void)hipFree(g->d_iadj);
   tile_destroy(g->tiles);
   g->tiles = nullptr;
   g->d_ioff = nullptr;
-  g->d_iadj = nullptr;
+  g->d_iadj = g->d_sadj = nullptr;
   g->d_off = g->d_off_ord = nullptr;
   g->d_adj = g->d_adj_ord = nullptr;
   g->d_ord_of = nullptr;

@@ -36,10 +36,11 @@ struct mlmq_graph {
   mlmq_config tuned{};
   int32_t sel_template = -1;  // the selector's top template (-1: the feature heuristic)
   mlmq_config sel_config{};   // that template as a configuration for this graph
-  // stepping solve (mlmq_step.cpp): in-rows of the graph that plain solves run
-  // on; both its out-rows and these are in ascending weight class
+  // stepping solve (mlmq_step.cpp): copies in ascending weight class of the
+  // out-rows and in-rows of the graph that plain solves run on
   bool step_ready = false;
-  int32_t* d_ioff = nullptr;   // [n+1]
+  uint64_t* d_sadj = nullptr;  // [m] out-rows
+  int32_t* d_ioff = nullptr;   // [n+1] in-rows
   uint64_t* d_iadj = nullptr;  // [m]
   mlmq_tiles* tiles = nullptr;  // tiled copy (null: the graph does not fall into tiles)
 };

@@ -64,7 +64,7 @@ StepLayout step_layout(const mlmq_graph* g, bool own_lab, bool own_out) {
 void graph_args(const mlmq_graph* g, StepArgs* a) {
   const bool ordered = g->d_ord_of != nullptr;
   a->off = ordered ? g->d_off_ord : g->d_off;
-  a->adj = ordered ? g->d_adj_ord : g->d_adj;
+  a->adj = g->d_sadj;
   a->ioff = g->d_ioff;
   a->iadj = g->d_iadj;
   a->ord_of = ordered ? g->d_ord_of : nullptr;
@@ -129,33 +129,35 @@ hipError_t step_prepare(mlmq_graph* g) {
   const uint32_t n = (uint32_t)g->n, m = (uint32_t)g->m;
   const bool ordered = g->d_ord_of != nullptr;
   const int32_t* off = ordered ? g->d_off_ord : g->d_off;
-  uint64_t** adj = ordered ? &g->d_adj_ord : &g->d_adj;
+  const uint64_t* adj = ordered ? g->d_adj_ord : g->d_adj;
   const uint32_t shift = class_shift(g->max_w);
-  uint64_t *sorted = nullptr, *raw = nullptr;
+  // The sorted rows are a copy: the queue worker keeps the caller's edge order
+  // (RMAT-20 with bucket queues: 60 ms in that order, 109 over sorted rows,
+  // whose runs of equal weight all go to one bucket at a time).
+  uint64_t* raw = nullptr;
   uint32_t* scratch = nullptr;
-  hipError_t e = hipMalloc(&sorted, 8ull * m);
+  hipError_t e = hipMalloc(&g->d_sadj, 8ull * m);
   if (e == hipSuccess) e = hipMalloc(&raw, 8ull * m);
   if (e == hipSuccess) e = hipMalloc(&scratch, 4ull * (n + 1ull + n / 4096 + 2));
   if (e == hipSuccess) e = hipMalloc(&g->d_ioff, 4ull * (n + 1ull));
   if (e == hipSuccess) e = hipMalloc(&g->d_iadj, 8ull * m);
-  if (e == hipSuccess) e = launch_sort_rows(off, *adj, sorted, n, shift, nullptr);
-  if (e == hipSuccess) e = launch_transpose(off, sorted, n, m, g->d_ioff, raw, scratch, nullptr);
+  if (e == hipSuccess) e = launch_sort_rows(off, adj, g->d_sadj, n, shift, nullptr);
+  if (e == hipSuccess) e = launch_transpose(off, g->d_sadj, n, m, g->d_ioff, raw, scratch, nullptr);
   if (e == hipSuccess) e = launch_sort_rows(g->d_ioff, raw, g->d_iadj, n, shift, nullptr);
   if (e == hipSuccess) e = hipStreamSynchronize(nullptr);
   (void)hipFree(raw);
   (void)hipFree(scratch);
   if (e != hipSuccess) {
-    (void)hipFree(sorted);
+    (void)hipFree(g->d_sadj);
     (void)hipFree(g->d_ioff);
     (void)hipFree(g->d_iadj);
+    g->d_sadj = nullptr;
     g->d_ioff = nullptr;
     g->d_iadj = nullptr;
     if (e != hipErrorOutOfMemory) return e;
-    (void)hipGetLastError();  // no room for the second copy: the graph keeps to the queue worker
+    (void)hipGetLastError();  // no room for the copies: the graph keeps to the queue worker
     return hipSuccess;
   }
-  (void)hipFree(*adj);
-  *adj = sorted;
   g->step_ready = true;
   return hipSuccess;
 }

@@ -183,7 +183,8 @@ hipError_t tile_prepare(mlmq_graph* g, const int32_t* off, const int32_t* col) {
     t->g.xcap = xcap;
   }
   (void)hipFree(tmp);
-  if (e == hipSuccess) e = tile_set_lds(lds);
+  // the same bound for every graph: a smaller one never lowers a larger one's
+  if (e == hipSuccess) e = tile_set_lds(di->lds_per_wg);
   if (e != hipSuccess) {
     tile_destroy(t);
     if (e != hipErrorOutOfMemory) return e;
