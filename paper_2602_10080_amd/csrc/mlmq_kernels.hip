@@ -1359,6 +1359,18 @@ __device__ __forceinline__ void run_query(Ctx& c) {
         if (try_terminate(c)) break;
         if ((++c.idle & 7u) == 0 && must_stop(c)) break;
         backoff(min(c.idle >> 2, 6u));
+        // A look at bucket rings reads two lines of each ring past the caches;
+        // three thousand idle waves doing so delay the working waves' atomics
+        // on the same lines. The longer a wave has been idle and the higher
+        // its index, the longer it waits, up to 48 x 3.4 us: the first 64
+        // waves look as often as ever, so new work is met at once. 512 x 512
+        // road-like grid, 3072 waves: 61 ms without the wait, 47 / 37 / 30
+        // with (index >> 8, idle >> 4) / (>> 6, >> 4) / (>> 6, all); RMAT-18
+        // 50 and 40 ms, RMAT-20 58 and 47, a 64 x 64 mesh 2.4 and 2.1. One
+        // ring is two lines and a ticket, and keeps the short waits.
+        if (c.q.nrings > 1 && !c.pq) {
+          for (uint32_t k = min(blockIdx.x >> 6, c.idle); k; --k) __builtin_amdgcn_s_sleep(127);
+        }
         t_idle += (uint64_t)wall_clock64() - t0;
         continue;
       }
