@@ -1,0 +1,100 @@
+"""Solves and levels in the library's own configuration (stepping and tiled
+solves) at the sizes and forms where their paths change, against the oracle.
+Distances are whole numbers: every comparison is exact."""
+import threading
+
+import numpy as np
+import pytest
+
+import graphgen as gg
+import oracle
+import paper_2602_10080_amd as mlmq
+
+pytestmark = pytest.mark.gpu
+torch = pytest.importorskip("torch")
+
+
+def directed(n, pairs, wmax, seed, zero_weights=False):
+    """Random directed graph whose last vertex has no edges at all."""
+    rng = np.random.default_rng(seed)
+    u, v = rng.integers(0, n - 1, pairs), rng.integers(0, n - 1, pairs)
+    w = rng.integers(0 if zero_weights else 1, wmax + 1, pairs).astype(np.uint32)
+    return gg.from_edges(n, u, v, w)
+
+
+def expect(csr, src):
+    return oracle.dijkstra(csr, src)
+
+
+def host(t):
+    return t if isinstance(t, np.ndarray) else t.cpu().numpy().view(np.uint32)
+
+
+FORMS = [
+    ("one tile", lambda: gg.grid(24, 37, 0.0, seed=1)),
+    ("tile edge", lambda: gg.grid(64, 64, 0.0, seed=2)),          # 4096 vertices: the most of one tile
+    ("just above one tile", lambda: gg.grid(17, 241, 0.0, seed=3)),  # 4097
+    ("many tiles, ragged", lambda: gg.grid(211, 307, 0.05, seed=4)),
+    ("skewed", lambda: gg.rmat(12, 16, seed=5)),
+    ("directed", lambda: directed(10007, 80000, 255, 6)),
+    ("zero weights", lambda: directed(10007, 80000, 3, 7, True)),
+    ("wide weights", lambda: directed(10007, 80000, 1 << 17, 8)),
+    ("sparse, mostly unreached", lambda: directed(10007, 9000, 255, 9)),
+]
+
+
+@pytest.mark.parametrize("name,make", FORMS, ids=[f[0] for f in FORMS])
+def test_default_solves_equal_the_oracle(name, make):
+    csr = make()
+    g = mlmq.Graph.from_csr(csr)
+    out = mlmq.new_dist(csr.n)
+    for src in (0, csr.n // 2, csr.n - 1):  # the directed graphs' last vertex is isolated
+        want = expect(csr, src)
+        np.testing.assert_array_equal(host(mlmq.sssp(g, src, out=out)), want, err_msg=f"{name} from {src}")
+        np.testing.assert_array_equal(mlmq.sssp(g, src, out=np.empty(csr.n, np.uint32)), want)
+        np.testing.assert_array_equal(host(mlmq.bfs(g, src, out=out)), oracle.bfs(csr, src))
+
+
+def test_queues_asked_for_give_the_same_distances():
+    for csr in (gg.grid(96, 80, 0.05, seed=1), gg.rmat(13, 8, seed=1)):
+        g = mlmq.Graph.from_csr(csr)
+        a = host(mlmq.sssp(g, 3)).copy()
+        cfg = mlmq.default_config(l0_rows=1, l1_type=2, l2_type=1, bmax=32, bnum=4, delta2_log2=7, delta1=128,
+                                  l1_cap=256, th_hub=0)
+        np.testing.assert_array_equal(host(mlmq.sssp(g, 3, config=cfg)), a)
+
+
+def test_a_graph_too_deep_for_steps():
+    """A long path with a hub at its end: neither tiles (the hub's degree) nor
+    the step limit take it, so the queue worker does."""
+    n, arms = 6000, 200
+    u = np.concatenate([np.arange(n - 1), np.full(arms, n - 1)])
+    v = np.concatenate([np.arange(1, n), n + np.arange(arms)])
+    total = n + arms
+    csr = gg.from_edges(total, u, v, np.full(len(u), 255, np.uint32))
+    g = mlmq.Graph.from_csr(csr)
+    np.testing.assert_array_equal(host(mlmq.sssp(g, 0)), expect(csr, 0))
+
+
+def test_batches_of_more_queries_than_a_group_and_from_two_threads():
+    graphs = [gg.rmat(10, 8, seed=1), gg.grid(40, 40, 0.05, seed=2), gg.grid(90, 90, 0.05, seed=3)]
+    handles = [mlmq.Graph.from_csr(c) for c in graphs]
+    queries = [(k, (17 * i) % graphs[k].n) for i in range(35) for k in range(3)]
+    want = {q: expect(graphs[q[0]], q[1]) for q in set(queries)}
+    failed = []
+
+    def work():
+        try:
+            outs, status = mlmq.sssp_batch([handles[k] for k, _ in queries], [s for _, s in queries])
+            assert not any(status)
+            for q, o in zip(queries, outs):
+                np.testing.assert_array_equal(host(o), want[q])
+        except BaseException as e:  # noqa: BLE001 (handed to the main thread)
+            failed.append(e)
+
+    threads = [threading.Thread(target=work) for _ in range(2)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert not failed, failed
