@@ -223,11 +223,14 @@ __device__ __forceinline__ void decide(Wave& c) {
         c.t0 = c.t1;
         c.t1 = c.t2;
         c.op = kOpPush;
-      } else {  // an empty stretch: on to the smallest label
+      } else {
+        // An empty stretch: on to the smallest label. The list that the last
+        // scan wrote is empty too, and this one writes the next: were it the
+        // same, a workgroup that starts late would find it no longer empty
+        // and push from it while it is being written.
         c.t0 = far_min;
         c.t1 = c.a.unit_w ? far_min + 1u : far_min;
         c.op = kOpScan;
-        next_list = false;
       }
     } else {
       // Pulling costs about three cache lines per vertex left (its bounds, a

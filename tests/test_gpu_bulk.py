@@ -98,3 +98,23 @@ def test_batches_of_more_queries_than_a_group_and_from_two_threads():
     for t in threads:
         t.join()
     assert not failed, failed
+
+
+def test_stretches_without_labels():
+    """Weights far above the width of a distance step: most scans find nothing
+    in it and go on to the smallest label. Shared launches of many rows have
+    workgroups that start when others of the same step have ended."""
+    csr = gg.rmat(16, 16, seed=9)
+    rng = np.random.default_rng(9)
+    w = np.where(rng.random(csr.m) < 0.97, csr.w % 4 + 1, csr.w * 1000).astype(np.uint32)
+    csr = gg.Csr(csr.n, csr.off, csr.col, w)
+    g = mlmq.Graph.from_csr(csr)
+    sources = [int(s) for s in gg.sample_sources(csr, 32, seed=1)]
+    want = [expect(csr, s) for s in sources]
+    for _ in range(4):
+        outs, status = mlmq.sssp_batch([g] * len(sources), sources)
+        assert not any(status)
+        for o, d in zip(outs, want):
+            np.testing.assert_array_equal(host(o), d)
+    for s, d in zip(sources[:4], want):
+        np.testing.assert_array_equal(host(mlmq.sssp(g, s)), d)
