@@ -1,7 +1,7 @@
 #!/usr/bin/env python3
 """Single-source SSSP throughput of the MLMQ library on one MI355X.
 
-One step = one complete single-source solve (init + persistent MLMQ kernel)
+One step = one complete single-source solve (init + solve kernels)
 on a graph already resident in HBM. The headline workload is RMAT scale 23
 (edge factor 16, symmetrised, ~258.7M directed edges, source = highest-degree
 vertex); the road-like 2048x2048 grid (p_drop 0.05, source = centre) is
@@ -9,7 +9,7 @@ measured in the same run. Inputs are seeded synthetic graphs.
 
 Prints one JSON line (see the repository's benchmark contract). GTEPS =
 directed edges leaving reachable vertices / solve time. The roofline entry
-prices the persistent kernel's algorithmic bytes, 12 B per reachable edge +
+prices the solve kernels' algorithmic bytes, 12 B per reachable edge +
 32 B per reachable vertex + 4 B per vertex, against 8 TB/s of HBM3E.
 The CPU baseline is the oracle (binary-heap Dijkstra, one core) on the same
 graph; its output also verifies the GPU distances.
@@ -17,6 +17,7 @@ graph; its output also verifies the GPU distances.
 import argparse
 import json
 import os
+import re
 import statistics
 import sys
 import time
@@ -53,30 +54,40 @@ def make_workload(name):
     raise SystemExit(f"unknown workload {name}")
 
 
-KERNEL_SRC = os.path.join(ROOT, "paper_2602_10080_amd", "csrc", "mlmq_kernels.hip")
+CSRC = os.path.join(ROOT, "paper_2602_10080_amd", "csrc")
+
+
+def kernel_sha():
+    """Hash of all device sources and of the rules that pick among them."""
+    import glob
+    import hashlib
+    h = hashlib.sha256()
+    for f in sorted(glob.glob(os.path.join(CSRC, "*"))):
+        if f.endswith((".hip", ".h", ".cpp")):
+            h.update(open(f, "rb").read())
+    return h.hexdigest()
 
 
 def measured_traffic(workload):
-    """HBM bytes per launch of the persistent kernel from the committed
+    """HBM bytes per solve from the committed
     rocprofv3 counter summary for this workload (FETCH_SIZE + WRITE_SIZE, each
     scaled by the same counter's reading for a copy of known size), or None if
-    there is none or the kernel source changed since it was taken."""
-    import hashlib
-    path = os.path.join(ROOT, "profiles", f"traffic_mlmq_worker_{workload}.json")
+    there is none or the sources changed since it was taken."""
+    path = os.path.join(ROOT, "profiles", f"traffic_solve_{workload}.json")
     if not os.path.exists(path):
         return None
     rec = json.load(open(path))
-    sha = hashlib.sha256(open(KERNEL_SRC, "rb").read()).hexdigest()
+    sha = kernel_sha()
     if rec.get("kernel_sha256") != sha:
         return None
     return rec
 
 
 def roofline(p):
-    """The roofline record of the persistent kernel on workload summary p:
-    algorithmic bytes per launch / its HIP-event duration against 8 TB/s, and,
-    when the committed counter summary matches the kernel source, the memory
-    traffic per launch: FETCH_SIZE and WRITE_SIZE scaled by a copy of known
+    """The roofline record of the solve kernels on workload summary p:
+    algorithmic bytes per solve / their HIP-event duration against 8 TB/s, and,
+    when the committed counter summary matches the sources, the memory
+    traffic per solve: FETCH_SIZE and WRITE_SIZE scaled by a copy of known
     size (traffic), the DRAM-bound 32-byte read sectors (calibrated 1.00 on
     the copy) and what that traffic is per second of the solve."""
     rec = measured_traffic(p["workload"])
@@ -515,22 +526,27 @@ def _counter_rows(path):
 
 
 def summarize_counters(root, workloads, warmup, steps):
-    """Per-launch counter values of the persistent kernel from the counter
+    """Per-solve counter values (all kernels of a solve) from the counter
     passes under root/<pass>/ (run with --bare, so each workload contributes
-    warmup + steps launches in order), the copy calibration from
+    warmup + steps solves in order), the copy calibration from
     root/copy_<pass>/, and the traffic record per workload."""
     import glob
-    import hashlib
     per = {w: {} for w in workloads}
     calib = {}
     for pas in COUNTER_PASSES:
         f = glob.glob(os.path.join(root, pas, "**", "*counter_collection.csv"), recursive=True)
         if f:
             rows = _counter_rows(f[0])
-            launches = [v for _, v in sorted(rows.items()) if "mlmq_worker" in v[0]]
+            launches = []  # a solve begins with its init kernel
+            for _, v in sorted(rows.items()):
+                if re.search(r"mlmq_(step_|tile_)?init\b", v[0]):
+                    launches.append((v[0], dict.fromkeys(v[1], 0.0)))
+                if launches and re.search(r"mlmq_(worker|step|tile_round|tile_init|unorder)", v[0]):
+                    for c, x in v[1].items():
+                        launches[-1][1][c] += x
             k = warmup + steps
             if len(launches) != k * len(workloads):
-                raise SystemExit(f"{pas}: {len(launches)} worker launches, expected {k * len(workloads)}")
+                raise SystemExit(f"{pas}: {len(launches)} solves, expected {k * len(workloads)}")
             for i, w in enumerate(workloads):
                 timed = launches[i * k + warmup:(i + 1) * k]
                 for c in timed[0][1]:
@@ -542,7 +558,7 @@ def summarize_counters(root, workloads, warmup, steps):
             big = [v for v in cp if v[1].get(COUNTER_PASSES[pas][0], 0) > 0]
             for c in big[-1][1]:
                 calib[c] = statistics.mean(v[1][c] for v in big[-3:])
-    sha = hashlib.sha256(open(KERNEL_SRC, "rb").read()).hexdigest()
+    sha = kernel_sha()
     copy_kib = 1 << 20  # the copy probe moves 1 GiB each way
     out = {}
     for w, c in per.items():
@@ -550,7 +566,7 @@ def summarize_counters(root, workloads, warmup, steps):
             continue
         fs = copy_kib / calib["FETCH_SIZE"] if "FETCH_SIZE" in calib else 1.0
         ws = copy_kib / calib["WRITE_SIZE"] if "WRITE_SIZE" in calib else 1.0
-        rec = dict(kernel="mlmq::mlmq_worker", workload=w, kernel_sha256=sha, launches_averaged=steps,
+        rec = dict(kernel="all kernels of a solve", workload=w, kernel_sha256=sha, launches_averaged=steps,
                    raw_fetch_kib_per_launch=c["FETCH_SIZE"], raw_write_kib_per_launch=c["WRITE_SIZE"],
                    fetch_scale=fs, write_scale=ws,
                    fetch_bytes_per_launch=c["FETCH_SIZE"] * 1024 * fs,
@@ -559,7 +575,7 @@ def summarize_counters(root, workloads, warmup, steps):
         if "TCC_EA0_RDREQ_DRAM_32B_sum" in c:
             rec["dram_read_bytes_per_launch"] = c["TCC_EA0_RDREQ_DRAM_32B_sum"] * 32
         out[w] = rec
-        with open(os.path.join(ROOT, "profiles", f"traffic_mlmq_worker_{w}.json"), "w") as fh:
+        with open(os.path.join(ROOT, "profiles", f"traffic_solve_{w}.json"), "w") as fh:
             json.dump(rec, fh, indent=1)
     print(json.dumps({w: {k: v for k, v in r.items() if k not in ("counters_per_launch", "copy_calibration")}
                       for w, r in out.items()}, indent=1))
@@ -585,7 +601,7 @@ def main():
     ap.add_argument("--bare", action="store_true",
                     help="only the warm-up and timed solves of each workload (for counter passes)")
     ap.add_argument("--summarize-counters", default="",
-                    help="directory of rocprofv3 counter passes: write profiles/traffic_mlmq_worker_<w>.json and exit")
+                    help="directory of rocprofv3 counter passes: write profiles/traffic_solve_<w>.json and exit")
     ap.add_argument("--pq-study", action="store_true",
                     help="also run the priority-queue case study (road512, rmat20) into the detail section")
     ap.add_argument("--copy-probe-mib", type=int, default=0,

@@ -64,11 +64,15 @@ extern "C" {
  * renumbered by decreasing degree, so that the labels of the high-degree
  * vertices, which most edges point to, share cache lines (on smaller graphs,
  * whose labels stay in cache anyway, it measured slower). Plain solves
- * (mlmq_sssp, mlmq_bfs, mlmq_autotune) run on that copy and gather the result
- * back into the caller's vertex order before they return; batches, servers,
- * mlmq_check, mlmq_latency_probe and mlmq_sssp_noalloc use the graph as given.
+ * (mlmq_sssp, mlmq_bfs, mlmq_autotune) and a batch's bulk solves (below) run on
+ * that copy and gather the result back into the caller's vertex order before
+ * they return; a batch's queue solves, servers, mlmq_check, mlmq_latency_probe and mlmq_sssp_noalloc use the graph as given.
  * The copy costs the graph's memory once more plus 4 bytes per vertex.
- * MLMQ_GRAPH_KEEP_ORDER leaves it out; MLMQ_GRAPH_DEGREE_ORDER makes it for
+ * Independent of that, a graph is also kept in the form of its bulk solve: tiles
+ * (meshes and road-like graphs; about 24 bytes an edge) or rows in and out
+ * sorted by weight (other graphs; 16 bytes an edge). A graph without room for
+ * it is solved by queues alone.
+ * MLMQ_GRAPH_KEEP_ORDER leaves the degree-ordered copy out; MLMQ_GRAPH_DEGREE_ORDER makes it for
  * any graph with edges. Setting both is an error.
  */
 #define MLMQ_GRAPH_KEEP_ORDER 2u
@@ -93,12 +97,13 @@ extern "C" {
                             L2MPQ (pnum > 1): pnum such heaps, each wave reading its own and writing
                             to all of them in turn */
 
-/* Counters a solve reports (summed over all waves). */
+/* Counters a solve reports (summed over all waves). A bulk solve has no queues:
+ * its l1_*, l2_*, hub_chunks, flushes, donations and *_ms of waves are 0. */
 typedef struct mlmq_stats {
   uint32_t struct_size;
   uint32_t status;         /* device status word of the last solve */
-  double kernel_ms;        /* device time of init + persistent kernel (HIP events) */
-  double worker_ms;        /* device time of the persistent kernel alone */
+  double kernel_ms;        /* device time of init + solve kernels (HIP events) */
+  double worker_ms;        /* device time of the solve kernels alone */
   uint64_t expansions;     /* work items that passed the stale check */
   uint64_t stale;          /* work items dropped as stale */
   uint64_t edges;          /* edges scanned */
@@ -121,6 +126,11 @@ typedef struct mlmq_stats {
  * Queue configuration (the search space of Section 3.5; every knob has a
  * default). Zero-initialise, set struct_size = sizeof(mlmq_config), call
  * mlmq_config_default, then change fields. Read only during a call.
+ *
+ * A solve whose queue fields all equal the graph's default choice (cfg == NULL,
+ * or mlmq_graph_config unchanged) and whose deadline is 0 or at least 50 ms runs
+ * as a bulk solve, without queues, where the graph has a form for one. Any
+ * other configuration runs on the queues it describes. The distances are the same.
  */
 typedef struct mlmq_config {
   uint32_t struct_size;
@@ -287,7 +297,9 @@ int mlmq_latency_probe(const mlmq_graph* g, uint32_t source, uint32_t hops, void
                        double* handoff_ns_out);
 
 /*
- * Many queries in one persistent launch. Query i solves graphs[i] from
+ * Many queries in one call. Queries left to the library's choice run as bulk
+ * solves that share their launches (up to 32 of a kind at a time); the others
+ * share one persistent launch. Query i solves graphs[i] from
  * sources[i] into dist_outs[i] (device memory, n_i uint32 each). cfgs may be
  * NULL (per-graph autotuned/default) or hold one config per query; launch
  * shape and stream come from cfgs[0] (or defaults). per_query_status may be
