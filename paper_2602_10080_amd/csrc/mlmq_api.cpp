@@ -768,6 +768,7 @@ const mlmq_config* resolve_config(const mlmq_graph* g, const mlmq_config* cfg, m
   if (g->has_tuned) {
     *tmp = g->tuned;
   } else if (g->sel_template < 0 || template_config(g, g->sel_template, tmp) != MLMQ_OK) {
+    *tmp = mlmq_config{};
     tmp->struct_size = sizeof(mlmq_config);
     default_config(tmp);
     heuristic_config(g, tmp);

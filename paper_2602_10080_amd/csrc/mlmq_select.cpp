@@ -182,7 +182,7 @@ int32_t selector_pick(const mlmq_features& f) { return kSelTrees ? ranked(f, nul
 
 // Template t (or the feature-driven default for t = -1) as a config for g.
 int template_config(const mlmq_graph* g, int32_t t, mlmq_config* out) {
-  mlmq_config c;
+  mlmq_config c{};  // default_config keeps stream and stats_out: none
   c.struct_size = sizeof(mlmq_config);
   default_config(&c);
   heuristic_config(g, &c);

@@ -1,0 +1,125 @@
+"""The library's host code on the CPU, over a stand-in device (tests/simt/host):
+the order of work on streams, waits and deadlines, memory that runs out, and
+which solver a call takes. Distances are whole numbers: every comparison is
+exact."""
+import ctypes
+import os
+import sys
+import threading
+import time
+
+import numpy as np
+import pytest
+
+import graphgen as gg
+import oracle
+import paper_2602_10080_amd as mlmq
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+ROOT = os.path.dirname(HERE)
+
+
+class Sim:
+    """The host code with its device, through the C ABI."""
+
+    def __init__(self, path):
+        self.lib = ctypes.CDLL(path)
+        mlmq._declare(self.lib)
+        self.lib.sim_alloc.restype = self.lib.sim_stream.restype = ctypes.c_void_p
+        self.lib.sim_alloc.argtypes = [ctypes.c_size_t]
+        self.lib.sim_hold.argtypes = [ctypes.c_void_p, ctypes.c_int]
+        self.lib.sim_fill.argtypes = [ctypes.c_void_p, ctypes.c_void_p, ctypes.c_uint32, ctypes.c_uint32]
+        self.lib.sim_set.argtypes = [ctypes.c_char_p, ctypes.c_double]
+        self.lib.sim_get.argtypes = [ctypes.c_char_p]
+        self.lib.sim_get.restype = ctypes.c_double
+
+    def set(self, **kw):
+        for k, v in kw.items():
+            self.lib.sim_set(k.encode(), float(v))
+
+    def count(self, what):
+        return int(self.lib.sim_get(what.encode()))
+
+    def graph(self, csr, flags=0):
+        h = ctypes.c_void_p()
+        off = csr.off32()
+        rc = self.lib.mlmq_graph_create(csr.n, csr.m, off.ctypes.data, csr.col.ctypes.data, csr.w.ctypes.data, flags,
+                                        ctypes.byref(h))
+        assert rc == 0, self.error()
+        return h
+
+    def error(self):
+        return self.lib.mlmq_last_error().decode()
+
+    def config(self, g, **kw):
+        c = mlmq.Config()
+        c.struct_size = ctypes.sizeof(c)
+        assert self.lib.mlmq_graph_config(g, ctypes.byref(c)) == 0
+        return c.copy(**kw)
+
+    def buffer(self, n):
+        """A device buffer and its contents as an array."""
+        p = self.lib.sim_alloc(4 * n)
+        return p, np.ctypeslib.as_array((ctypes.c_uint32 * n).from_address(p))
+
+    def sssp(self, g, src, out, cfg=None, bfs=False):
+        f = self.lib.mlmq_bfs if bfs else self.lib.mlmq_sssp
+        return f(g, src, out, ctypes.byref(cfg) if cfg is not None else None)
+
+    def batch(self, queries, cfgs=None):
+        """queries: (graph, source, buffer address); the call's status and each query's."""
+        n = len(queries)
+        st = (ctypes.c_int32 * n)(*[99] * n)
+        rc = self.lib.mlmq_sssp_batch((ctypes.c_void_p * n)(*[q[0].value for q in queries]),
+                                      (ctypes.c_uint32 * n)(*[q[1] for q in queries]),
+                                      (ctypes.c_void_p * n)(*[q[2] for q in queries]), n,
+                                      (ctypes.c_void_p * n)(*[ctypes.addressof(c) for c in cfgs]) if cfgs else None, st)
+        return rc, list(st)
+
+
+@pytest.fixture(scope="module")
+def _sim():
+    sys.path.insert(0, os.path.join(HERE, "simt"))
+    import build_host_sim
+    return Sim(build_host_sim.build(os.path.join(ROOT, "_build", "simt")))
+
+
+@pytest.fixture
+def sim(_sim):
+    _sim.set(steps=6, worker_ms=0, step_ms=0, room=-1, largest=-1, reset=1)
+    yield _sim
+    _sim.set(steps=6, worker_ms=0, step_ms=0, room=-1, largest=-1)
+
+
+ROAD = gg.grid(70, 80, 0.05, seed=1)      # several tiles
+MESH = gg.grid(20, 30, 0.0, seed=2)       # one tile
+SKEWED = gg.rmat(12, 8, seed=3)           # steps
+QUEUES = dict(l0_rows=1, l1_type=2, l2_type=1, bmax=32, bnum=4, delta2_log2=7, delta1=128, l1_cap=256, th_hub=0)
+
+
+def test_routes_and_results(sim):
+    for csr, kernel in ((ROAD, "tile"), (MESH, "tile"), (SKEWED, "step")):
+        g = sim.graph(csr)
+        p, out = sim.buffer(csr.n)
+        host = np.zeros(csr.n, np.uint32)
+        for how, bulk in ((None, True), (sim.config(g), True), (sim.config(g, **QUEUES), False)):
+            sim.set(reset=1)
+            assert sim.sssp(g, 5, p, how) == 0
+            np.testing.assert_array_equal(out, oracle.dijkstra(csr, 5))
+            assert (sim.count(kernel) > 0, sim.count("worker") > 0) == (bulk, not bulk)
+        assert sim.sssp(g, 5, host.ctypes.data) == 0 and sim.sssp(g, 7, p, bfs=True) == 0
+        np.testing.assert_array_equal(host, oracle.dijkstra(csr, 5))
+        np.testing.assert_array_equal(out, oracle.bfs(csr, 7))
+
+
+def test_calls_without_a_configuration(sim):
+    """A NULL configuration has no stream and no place for counters, whatever
+    the stack held before; in a batch too."""
+    for csr in (ROAD, MESH, SKEWED):
+        g = sim.graph(csr)
+        p, out = sim.buffer(csr.n)
+        for call in (lambda: sim.sssp(g, 5, p), lambda: sim.sssp(g, 5, p, bfs=True),
+                     lambda: sim.lib.mlmq_sssp_noalloc(g, 5, p, None), lambda: sim.batch([(g, 5, p)])[0]):
+            sim.lib.sim_dirty_stack()
+            assert call() == 0, sim.error()
+        np.testing.assert_array_equal(out, oracle.dijkstra(csr, 5))
