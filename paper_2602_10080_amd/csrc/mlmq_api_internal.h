@@ -123,6 +123,8 @@ bool bulk_solves(const mlmq_graph* g, const mlmq_config& c, bool unit_weights);
 // Such a solve; *finished = false: nothing was decided, the queue worker must solve.
 int run_bulk(const mlmq_graph* g, uint32_t source, uint32_t* dist_out, const mlmq_config& c, bool unit_weights,
              bool dev_out, bool* finished);
+// Makes the streams wait for what `after` (null: the null stream) holds so far.
+hipError_t start_after(hipStream_t after, const hipStream_t* streams, int count);
 // Several, into device buffers; status[i] for each i of which, *left: undecided.
 int run_bulk_batch(const mlmq_graph* const* graphs, const uint32_t* sources, uint32_t* const* dist_outs,
                    const mlmq_config* conf, const std::vector<int32_t>& which, hipStream_t after,

@@ -73,6 +73,7 @@ static int queue_batch(const mlmq_graph* const* all_graphs, const uint32_t* all_
   LaunchShape shape;
   rc = launch_shape(lc, l1cap, two, stage, pq, &shape);
   if (rc) return rc;
+  // (the null stream cannot be captured)
   hipStream_t stream = lc.stream ? reinterpret_cast<hipStream_t>(lc.stream) : internal_stream();
   // Largest queries first, so the long ones start early (LPT order).
   std::vector<int32_t> order((size_t)nq);
@@ -128,7 +129,8 @@ static int queue_batch(const mlmq_graph* const* all_graphs, const uint32_t* all_
                                      a.cap_wait_ticks, (uint64_t)a.l1_cap, (uint64_t)a.l1_two, (uint64_t)a.stage,
                                      (uint64_t)a.waves, (uint64_t)(uintptr_t)d_desc, (uint64_t)(uintptr_t)d_batch,
                                      (uint64_t)(uintptr_t)d_res, (uint64_t)(uintptr_t)d_beats};
-  hipError_t e = hipMemcpyAsync(d_desc, h_desc, sizeof(QueryDesc) * nq, hipMemcpyHostToDevice, stream);
+  hipError_t e = lc.stream ? hipSuccess : start_after(nullptr, &stream, 1);
+  if (e == hipSuccess) e = hipMemcpyAsync(d_desc, h_desc, sizeof(QueryDesc) * nq, hipMemcpyHostToDevice, stream);
   if (e == hipSuccess && (!slab->graph_exec || slab->graph_key != key)) {
     if (slab->graph_exec) {
       (void)hipGraphExecDestroy(slab->graph_exec);

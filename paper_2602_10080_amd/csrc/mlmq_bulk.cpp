@@ -380,9 +380,21 @@ void BulkGroup::finish(int32_t* status, std::vector<int32_t>* left) {
 
 }  // namespace
 
+// The library's own streams do not wait for the null stream by themselves:
+// what the caller has put on its stream (a fill of an output buffer, say), the
+// null stream included, comes before what they are given next.
+hipError_t start_after(hipStream_t after, const hipStream_t* streams, int count) {
+  hipEvent_t ev = nullptr;
+  hipError_t e = hipEventCreateWithFlags(&ev, hipEventDisableTiming);
+  if (e == hipSuccess) e = hipEventRecord(ev, after);
+  for (int i = 0; i < count && e == hipSuccess; ++i) e = hipStreamWaitEvent(streams[i], ev, 0);
+  if (ev) (void)hipEventDestroy(ev);
+  return e;
+}
+
 // Queries `which` of a batch in groups that share their launches, on streams of
-// their own, which start after what `after` (if given) holds so far. Those that
-// nothing was decided for come back in *left.
+// their own, which start after what `after` holds so far. Those that nothing was
+// decided for come back in *left.
 int run_bulk_batch(const mlmq_graph* const* graphs, const uint32_t* sources, uint32_t* const* dist_outs,
                    const mlmq_config* conf, const std::vector<int32_t>& which, hipStream_t after,
                    uint32_t timeout_ms, int32_t* status, std::vector<int32_t>* left) {
@@ -392,17 +404,10 @@ int run_bulk_batch(const mlmq_graph* const* graphs, const uint32_t* sources, uin
   Streams* streams = nullptr;
   hipError_t e = streams_acquire(&streams);
   if (e != hipSuccess) return hip_fail(e, "batch streams");
-  if (after) {
-    hipEvent_t ev = nullptr;
-    e = hipEventCreateWithFlags(&ev, hipEventDisableTiming);
-    if (e == hipSuccess) e = hipEventRecord(ev, after);
-    for (hipStream_t s : streams->s)
-      if (e == hipSuccess) e = hipStreamWaitEvent(s, ev, 0);
-    if (ev) (void)hipEventDestroy(ev);
-    if (e != hipSuccess) {
-      streams_release(streams);
-      return hip_fail(e, "batch streams");
-    }
+  e = start_after(after, streams->s, kLanes);
+  if (e != hipSuccess) {
+    streams_release(streams);
+    return hip_fail(e, "batch streams");
   }
   BulkGroup group[kLanes];
   size_t next[kLanes] = {};

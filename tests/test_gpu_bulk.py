@@ -118,3 +118,22 @@ def test_stretches_without_labels():
             np.testing.assert_array_equal(host(o), d)
     for s, d in zip(sources[:4], want):
         np.testing.assert_array_equal(host(mlmq.sssp(g, s)), d)
+
+
+@pytest.mark.parametrize("queues", [False, True])
+def test_a_batch_starts_after_work_on_the_default_stream(queues):
+    """Fills of the output buffers wait behind a long kernel when the batch is
+    called; the solves come after them."""
+    graphs = [gg.rmat(12, 16, seed=5), gg.grid(90, 90, 0.05, seed=3), gg.grid(30, 30, 0.0, seed=2)]
+    handles = [mlmq.Graph.from_csr(c) for c in graphs]
+    outs = [mlmq.new_dist(c.n) for c in graphs]
+    cfg = mlmq.default_config(l0_rows=1, l1_type=2, l2_type=1, bmax=32, bnum=4, delta2_log2=7, delta1=128, l1_cap=256,
+                              th_hub=0) if queues else None
+    for _ in range(2):
+        torch.cuda._sleep(100_000_000)
+        for o in outs:
+            o.fill_(7)
+        _, status = mlmq.sssp_batch(handles, [3] * 3, outs=outs, configs=[cfg] * 3)
+        assert not any(status)
+        for c, o in zip(graphs, outs):
+            np.testing.assert_array_equal(host(o), expect(c, 3))

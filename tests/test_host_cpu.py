@@ -123,3 +123,22 @@ def test_calls_without_a_configuration(sim):
             sim.lib.sim_dirty_stack()
             assert call() == 0, sim.error()
         np.testing.assert_array_equal(out, oracle.dijkstra(csr, 5))
+
+
+@pytest.mark.parametrize("queues", [False, True])
+def test_batch_starts_after_work_on_the_null_stream(sim, queues):
+    """A fill of the output buffers that still waits on the null stream comes
+    before the batch's solves, whichever solver they take."""
+    work = [(ROAD, sim.graph(ROAD)), (SKEWED, sim.graph(SKEWED)), (MESH, sim.graph(MESH))]
+    outs = [sim.buffer(c.n) for c, _ in work]
+    cfgs = [sim.config(g, **(QUEUES if queues else {})) for _, g in work]
+    sim.lib.sim_hold(None, 1)
+    for (c, _), (p, _o) in zip(work, outs):
+        sim.lib.sim_fill(None, p, c.n, 7)
+    t = threading.Timer(0.2, sim.lib.sim_hold, (None, 0))
+    t.start()
+    rc, st = sim.batch([(g, 3, p) for (_, g), (p, _o) in zip(work, outs)], cfgs)
+    t.join()
+    assert rc == 0 and not any(st)
+    for (c, _), (_p, o) in zip(work, outs):
+        np.testing.assert_array_equal(o, oracle.dijkstra(c, 3))
