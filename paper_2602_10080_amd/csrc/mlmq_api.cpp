@@ -469,17 +469,18 @@ QueryDesc make_desc(const mlmq_graph* g, const mlmq_config& c, const QueryPlan& 
   return d;
 }
 
+static void slab_destroy(Slab* s) {
+  if (s->graph_exec) (void)hipGraphExecDestroy(s->graph_exec);
+  if (s->done) (void)hipEventDestroy(s->done);
+  (void)hipFree(s->dev);
+  (void)hipHostFree(s->host);
+  delete s;
+}
+
 // Device-memory pool: slabs are kept and reused by later calls.
 struct Pool {
   std::mutex mu;
   std::vector<Slab*> free_list;
-  ~Pool() {
-    for (Slab* s : free_list) {
-      (void)hipFree(s->dev);
-      (void)hipHostFree(s->host);
-      delete s;
-    }
-  }
 };
 static Pool& pool() {
   static Pool* p = new Pool();  // never destroyed: the HIP runtime may be gone at exit
@@ -519,11 +520,7 @@ int slab_acquire(size_t dev_bytes, size_t host_bytes, Slab** out) {
       std::lock_guard<std::mutex> lk(pool().mu);
       drop.swap(pool().free_list);
     }
-    for (Slab* d : drop) {
-      (void)hipFree(d->dev);
-      (void)hipHostFree(d->host);
-      delete d;
-    }
+    for (Slab* d : drop) slab_destroy(d);
     s = new Slab();
     s->dev_bytes = align_up(dev_bytes, 1 << 20);
     s->host_bytes = align_up(std::max<size_t>(host_bytes, 4096), 4096);
@@ -551,12 +548,7 @@ void pool_trim() {
     std::lock_guard<std::mutex> lk(pool().mu);
     drop.swap(pool().free_list);
   }
-  for (Slab* d : drop) {
-    if (d->graph_exec) (void)hipGraphExecDestroy(d->graph_exec);
-    (void)hipFree(d->dev);
-    (void)hipHostFree(d->host);
-    delete d;
-  }
+  for (Slab* d : drop) slab_destroy(d);
 }
 
 // Launch shape for a config: workgroup size, LDS bytes and the number of

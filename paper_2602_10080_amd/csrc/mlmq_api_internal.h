@@ -70,6 +70,7 @@ struct Slab {
   size_t dev_bytes = 0;
   void* host = nullptr;
   size_t host_bytes = 0;
+  hipEvent_t done = nullptr;            // marks the last launch of a bulk solve
   hipGraphExec_t graph_exec = nullptr;  // cached captured launch (batch)
   std::vector<uint64_t> graph_key;      // every argument baked into graph_exec
 };

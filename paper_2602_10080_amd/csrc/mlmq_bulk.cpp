@@ -5,6 +5,7 @@
 
 #include <algorithm>
 #include <cstring>
+#include <memory>
 #include <mutex>
 #include <vector>
 
@@ -78,7 +79,7 @@ hipError_t BulkSolve::launch(uint32_t i) {
 }
 
 int BulkSolve::prepare(const mlmq_graph* g, uint32_t source, uint32_t* dist_out, const mlmq_config& c,
-                       hipStream_t stream, bool unit_weights, bool dev_out, bool timed) {
+                       hipStream_t stream, bool unit_weights, bool dev_out, bool timed, Deadline* deadline) {
   *this = BulkSolve();
   g_ = g;
   c_ = c;
@@ -86,8 +87,7 @@ int BulkSolve::prepare(const mlmq_graph* g, uint32_t source, uint32_t* dist_out,
   stream_ = stream;
   unit_ = unit_weights;
   dev_out_ = dev_out;
-  timeout_ms_ = c.timeout_ms ? c.timeout_ms : 60000;
-  end_ = std::chrono::steady_clock::now() + std::chrono::milliseconds(timeout_ms_);
+  deadline_ = deadline;
   const bool ordered = g->d_ord_of != nullptr;
   const size_t mem = align_up(g->tiles ? tile_memory(g, !dev_out) : step_memory(g, ordered || !dev_out, ordered && !dev_out), 256);
   const size_t words = std::max(sizeof(StepHost), sizeof(TileHost));
@@ -139,12 +139,14 @@ bool BulkSolve::advance() {
       continue;
     }
     if ((++spins_ & 1023u) == 0) {
-      if (std::chrono::steady_clock::now() > end_) {
+      const uint32_t begun = *begun_;
+      if (begun) deadline_->begun();
+      if (deadline_->over()) {
         late_ = true;
         return true;
       }
+      if (issued_ + 1 >= limit_ && begun >= issued_) return true;  // no launch is left
       const hipError_t q = hipStreamQuery(stream_);
-      if (q == hipSuccess && issued_ + 1 >= limit_) return true;  // every launch has run
       if (q != hipSuccess && q != hipErrorNotReady) e_ = q;
     }
     return e_ != hipSuccess;
@@ -152,12 +154,32 @@ bool BulkSolve::advance() {
   return true;
 }
 
+// A wait on the stream itself would also wait for what other threads go on
+// putting there.
+hipError_t wait_issued(hipStream_t stream, Slab* slab, Deadline::clk::time_point by) {
+  hipError_t e = slab->done ? hipSuccess : hipEventCreateWithFlags(&slab->done, hipEventDisableTiming);
+  if (e == hipSuccess) e = hipEventRecord(slab->done, stream);
+  if (e != hipSuccess) return e;
+  for (uint32_t spins = 1; (e = hipEventQuery(slab->done)) == hipErrorNotReady; ++spins) {
+    if ((spins & 1023u) == 0 && Deadline::clk::now() > by) break;
+    __builtin_ia32_pause();
+  }
+  return e;
+}
+
 int BulkSolve::finish(bool* finished) {
+  return finish(finished, no_room_ ? hipSuccess : wait_issued(stream_, slab_, deadline_->drained_by()));
+}
+
+int BulkSolve::finish(bool* finished, hipError_t waited) {
   *finished = !no_room_;
   if (no_room_) return MLMQ_OK;
-  hipError_t q;
-  while ((q = hipStreamQuery(stream_)) == hipErrorNotReady) __builtin_ia32_pause();
-  if (e_ == hipSuccess) e_ = q;
+  if (waited == hipErrorNotReady) {
+    // launches of this solve are still to come: its memory is never reused
+    return set_error(MLMQ_ERR_TIMEOUT, "the stream did not get through the solve within its timeout of %u ms",
+                     deadline_->ms());
+  }
+  if (e_ == hipSuccess) e_ = waited;
   const bool done = e_ == hipSuccess && __atomic_load_n(state_, __ATOMIC_ACQUIRE) == 1;
   int rc = MLMQ_OK;
   if (e_ != hipSuccess)
@@ -165,7 +187,7 @@ int BulkSolve::finish(bool* finished) {
   else if (done)
     rc = deliver();
   else if (late_)
-    rc = set_error(MLMQ_ERR_TIMEOUT, "the solve overran its timeout of %u ms", timeout_ms_);
+    rc = set_error(MLMQ_ERR_TIMEOUT, "the solve overran its timeout of %u ms", deadline_->ms());
   else
     *finished = false;  // out of launches, or a list ran over
   for (hipEvent_t ev : {ev0_, evw_, ev1_})
@@ -235,8 +257,10 @@ bool bulk_solves(const mlmq_graph* g, const mlmq_config& c, bool unit_weights) {
 
 int run_bulk(const mlmq_graph* g, uint32_t source, uint32_t* dist_out, const mlmq_config& c, bool unit_weights,
              bool dev_out, bool* finished) {
+  Deadline deadline(c.timeout_ms);
   BulkSolve s;
-  const int rc = s.prepare(g, source, dist_out, c, reinterpret_cast<hipStream_t>(c.stream), unit_weights, dev_out, true);
+  const int rc =
+      s.prepare(g, source, dist_out, c, reinterpret_cast<hipStream_t>(c.stream), unit_weights, dev_out, true, &deadline);
   *finished = true;
   if (rc) return rc;
   s.begin();
@@ -255,7 +279,8 @@ class BulkGroup {
              const mlmq_config* conf, const std::vector<int32_t>& which, size_t* next, hipStream_t stream,
              uint32_t timeout_ms, int32_t* status, std::vector<int32_t>* left);
   bool advance();
-  void finish(int32_t* status, std::vector<int32_t>* left);
+  // False: the stream did not get through; it must be left alone.
+  bool finish(int32_t* status, std::vector<int32_t>* left);
   bool busy() const { return !solves_.empty(); }
 
  private:
@@ -266,7 +291,7 @@ class BulkGroup {
   bool tiled_ = false, late_ = false;
   uint32_t blocks_ = 0, limit_ = 0, issued_ = 0, spins_ = 0;
   hipError_t e_ = hipSuccess;
-  std::chrono::steady_clock::time_point end_{};
+  std::shared_ptr<Deadline> deadline_;
 
   hipError_t launch(uint32_t i) {
     const uint32_t n = (uint32_t)solves_.size();
@@ -281,6 +306,7 @@ void BulkGroup::begin(const mlmq_graph* const* graphs, const uint32_t* sources, 
                       uint32_t timeout_ms, int32_t* status, std::vector<int32_t>* left) {
   *this = BulkGroup();
   stream_ = stream;
+  deadline_ = std::make_shared<Deadline>(timeout_ms);
   size_t bytes = 0;
   uint32_t most = 0, tiles = 0;
   while (*next < which.size() && solves_.size() < kGroup) {
@@ -291,7 +317,7 @@ void BulkGroup::begin(const mlmq_graph* const* graphs, const uint32_t* sources, 
     mlmq_config c = conf[i];
     c.timeout_ms = timeout_ms;
     BulkSolve s;
-    const int rc = s.prepare(g, sources[i], dist_outs[i], c, stream, false, true, false);
+    const int rc = s.prepare(g, sources[i], dist_outs[i], c, stream, false, true, false, deadline_.get());
     if (s.no_room() && !solves_.empty()) break;  // as many as fit now, the others after them
     ++*next;
     if (rc) {
@@ -321,7 +347,6 @@ void BulkGroup::begin(const mlmq_graph* const* graphs, const uint32_t* sources, 
   blocks_ = std::min(most, std::max((all + n - 1u) / n, most / 16u + 1u));
   if (tiled_) blocks_ = std::max(blocks_, (tiles + kTileVisits - 1u) / kTileVisits);
   limit_ = tiled_ ? kTileRounds : kStepMax;
-  end_ = std::chrono::steady_clock::now() + std::chrono::milliseconds(timeout_ms ? timeout_ms : 60000);
   const size_t one = tiled_ ? sizeof(TileArgs) : sizeof(StepArgs);
   if (slab_acquire(one * n, one * n, &args_) != MLMQ_OK) {
     e_ = hipErrorOutOfMemory;  // finish() reports it
@@ -353,29 +378,33 @@ bool BulkGroup::advance() {
       continue;
     }
     if ((++spins_ & 1023u) == 0) {
-      if (std::chrono::steady_clock::now() > end_) {
+      if (begun) deadline_->begun();
+      if (deadline_->over()) {
         late_ = true;
         return true;
       }
+      if (issued_ + 1 >= limit_ && begun >= issued_) return true;
       const hipError_t q = hipStreamQuery(stream_);
-      if (q == hipSuccess && issued_ + 1 >= limit_) return true;
       if (q != hipSuccess && q != hipErrorNotReady) e_ = q;
     }
     return e_ != hipSuccess;
   }
 }
 
-void BulkGroup::finish(int32_t* status, std::vector<int32_t>* left) {
+bool BulkGroup::finish(int32_t* status, std::vector<int32_t>* left) {
+  Slab* const any = args_ ? args_ : solves_[0].slab();
+  const hipError_t waited = wait_issued(stream_, any, deadline_->drained_by());
   for (size_t i = 0; i < solves_.size(); ++i) {
     if (e_ != hipSuccess) solves_[i].fail(e_);
     if (late_) solves_[i].set_late();
     bool finished = true;
-    status[query_[i]] = solves_[i].finish(&finished);  // waits for the stream
+    status[query_[i]] = solves_[i].finish(&finished, waited);
     if (!finished) left->push_back(query_[i]);
   }
   solves_.clear();
-  slab_release(args_);
+  if (waited != hipErrorNotReady) slab_release(args_);
   args_ = nullptr;
+  return waited != hipErrorNotReady;
 }
 
 }  // namespace
@@ -411,16 +440,21 @@ int run_bulk_batch(const mlmq_graph* const* graphs, const uint32_t* sources, uin
   }
   BulkGroup group[kLanes];
   size_t next[kLanes] = {};
+  bool stuck[kLanes] = {};
   for (bool more = true; more;) {
     more = false;
     for (int k = 0; k < kLanes; ++k) {
+      if (stuck[k]) {
+        for (; next[k] < of[k].size(); ++next[k])
+          status[of[k][next[k]]] = set_error(MLMQ_ERR_TIMEOUT, "the batch's stream did not get through in time");
+      }
       if (!group[k].busy() && next[k] < of[k].size())
         group[k].begin(graphs, sources, dist_outs, conf, of[k], &next[k], streams->s[k], timeout_ms, status, left);
-      if (group[k].busy() && group[k].advance()) group[k].finish(status, left);
+      if (group[k].busy() && group[k].advance()) stuck[k] = !group[k].finish(status, left);
       more = more || group[k].busy() || next[k] < of[k].size();
     }
   }
-  streams_release(streams);
+  if (std::find(stuck, stuck + kLanes, true) == stuck + kLanes) streams_release(streams);
   return MLMQ_OK;
 }
 

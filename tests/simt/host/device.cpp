@@ -554,6 +554,10 @@ void sim_fill(void* s, uint32_t* p, uint32_t n, uint32_t v) {
     return true;
   });
 }
+void sim_wait(void* s, double ms) {
+  std::lock_guard<std::recursive_mutex> lk(g_mu);
+  enqueue(static_cast<hipStream_t>(s), timed(ms, [] {}));
+}
 void sim_set(const char* what, double v) {
   std::lock_guard<std::recursive_mutex> lk(g_mu);
   const std::string w = what;

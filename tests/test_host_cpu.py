@@ -29,6 +29,7 @@ class Sim:
         self.lib.sim_alloc.argtypes = [ctypes.c_size_t]
         self.lib.sim_hold.argtypes = [ctypes.c_void_p, ctypes.c_int]
         self.lib.sim_fill.argtypes = [ctypes.c_void_p, ctypes.c_void_p, ctypes.c_uint32, ctypes.c_uint32]
+        self.lib.sim_wait.argtypes = [ctypes.c_void_p, ctypes.c_double]
         self.lib.sim_set.argtypes = [ctypes.c_char_p, ctypes.c_double]
         self.lib.sim_get.argtypes = [ctypes.c_char_p]
         self.lib.sim_get.restype = ctypes.c_double
@@ -142,3 +143,84 @@ def test_batch_starts_after_work_on_the_null_stream(sim, queues):
     assert rc == 0 and not any(st)
     for (c, _), (_p, o) in zip(work, outs):
         np.testing.assert_array_equal(o, oracle.dijkstra(c, 3))
+
+
+def test_deadline_counts_from_the_device_s_start(sim):
+    """Earlier work on the stream outlasts the deadline; the solve itself does not."""
+    g = sim.graph(ROAD)
+    p, out = sim.buffer(ROAD.n)
+    stream = sim.lib.sim_stream()
+    for call in ("single", "batch"):
+        out[:] = 1
+        sim.lib.sim_hold(stream, 1)
+        sim.lib.sim_fill(stream, p, ROAD.n, 7)
+        t = threading.Timer(0.3, sim.lib.sim_hold, (stream, 0))
+        t.start()
+        cfg = sim.config(g, stream=stream, timeout_ms=100)
+        rc = sim.sssp(g, 3, p, cfg) if call == "single" else sim.batch([(g, 3, p)], [cfg])[0]
+        t.join()
+        assert rc == 0, (call, sim.error())
+        np.testing.assert_array_equal(out, oracle.dijkstra(ROAD, 3))
+
+
+def test_a_solve_that_takes_too_long_ends_at_its_deadline(sim):
+    for csr in (ROAD, SKEWED):
+        g = sim.graph(csr)
+        p, out = sim.buffer(csr.n)
+        for call in ("single", "batch"):
+            sim.set(steps=10**6, step_ms=20)
+            t0 = time.time()
+            cfg = sim.config(g, timeout_ms=100)
+            rc = sim.sssp(g, 3, p, cfg) if call == "single" else sim.batch([(g, 3, p)], [cfg])[0]
+            assert rc == -5 and time.time() - t0 < 2.0, (call, rc)
+            sim.set(steps=6, step_ms=0)
+            assert sim.sssp(g, 3, p) == 0  # the memory of the late solve is whole
+            np.testing.assert_array_equal(out, oracle.dijkstra(csr, 3))
+
+
+@pytest.mark.parametrize("call", ["single", "batch"])
+def test_a_stream_that_never_gets_there_is_not_waited_for(sim, call):
+    """As the queue worker's: the call returns some seconds after its deadline
+    and what its launches may still touch is not given to another call."""
+    g = sim.graph(SKEWED)
+    p, out = sim.buffer(SKEWED.n)
+    stream = sim.lib.sim_stream()
+    sim.lib.sim_hold(stream, 1)
+    cfg = sim.config(g, stream=stream, timeout_ms=50)
+    t0 = time.time()
+    rc = sim.sssp(g, 3, p, cfg) if call == "single" else sim.batch([(g, 3, p)], [cfg])[0]
+    assert rc == -5 and 3.0 < time.time() - t0 < 12.0
+    q, other = sim.buffer(SKEWED.n)
+    for _ in range(3):
+        assert sim.sssp(g, 4, q) == 0 and sim.batch([(g, 4, q)])[0] == 0
+    sim.lib.sim_hold(stream, 0)  # the late launches run now
+    sim.lib.sim_pump()
+    np.testing.assert_array_equal(other, oracle.dijkstra(SKEWED, 4))
+
+
+def test_a_solve_does_not_wait_for_what_others_put_on_its_stream(sim):
+    """Another thread goes on putting work on the same stream."""
+    g = sim.graph(SKEWED)
+    p, out = sim.buffer(SKEWED.n)
+    q, _ = sim.buffer(SKEWED.n)
+    stream = sim.lib.sim_stream()
+    stop = threading.Event()
+
+    def keep_busy():
+        while not stop.is_set():
+            sim.lib.sim_wait(stream, 2.0)  # two milliseconds of work, always two of them ahead
+            time.sleep(0.0015)
+
+    t = threading.Thread(target=keep_busy)
+    t.start()
+    end = threading.Timer(4.0, stop.set)
+    end.start()
+    time.sleep(0.05)
+    t0 = time.time()
+    rc = sim.sssp(g, 3, p, sim.config(g, stream=stream))
+    took = time.time() - t0
+    stop.set()
+    t.join()
+    end.cancel()
+    assert rc == 0 and took < 2.0, took
+    np.testing.assert_array_equal(out, oracle.dijkstra(SKEWED, 3))
