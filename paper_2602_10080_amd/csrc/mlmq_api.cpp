@@ -820,9 +820,10 @@ void heuristic_config(const mlmq_graph* g, mlmq_config* c) {
 }
 
 // One solve attempt sequence (with capacity retries) on a slab.
-int run_single(const mlmq_graph* g, uint32_t source, uint32_t* dist_out, const mlmq_config& c, bool unit_weights) {
-  int rc = check_config(&c);
+int run_single(const mlmq_graph* g, uint32_t source, uint32_t* dist_out, const mlmq_config& cfg, bool unit_weights) {
+  int rc = check_config(&cfg);
   if (rc) return rc;
+  mlmq_config c = cfg;
   hipStream_t stream = reinterpret_cast<hipStream_t>(c.stream);
   const bool dev_out = is_device_ptr(dist_out);
   // power-law graphs are solved on their degree-ordered copy, whose labels
@@ -830,7 +831,7 @@ int run_single(const mlmq_graph* g, uint32_t source, uint32_t* dist_out, const m
   const bool ordered = g->d_ord_of != nullptr;
   if (bulk_solves(g, c, unit_weights)) {
     bool finished = false;
-    rc = run_bulk(g, source, dist_out, c, unit_weights, dev_out, &finished);
+    rc = run_bulk(g, source, dist_out, c, unit_weights, dev_out, &finished, &c.timeout_ms);
     if (finished) return rc;
   }
   LaunchShape shape;

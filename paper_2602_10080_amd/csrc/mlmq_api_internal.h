@@ -121,15 +121,17 @@ void tile_destroy(mlmq_tiles* t);
 // Whether a solve on g with c runs as a sequence of launches (stepping or
 // tiled) instead of the queue worker.
 bool bulk_solves(const mlmq_graph* g, const mlmq_config& c, bool unit_weights);
-// Such a solve; *finished = false: nothing was decided, the queue worker must solve.
+// Such a solve; *finished = false: nothing was decided, the queue worker must
+// solve in the *left_ms that are left of the deadline.
 int run_bulk(const mlmq_graph* g, uint32_t source, uint32_t* dist_out, const mlmq_config& c, bool unit_weights,
-             bool dev_out, bool* finished);
+             bool dev_out, bool* finished, uint32_t* left_ms);
 // Makes the streams wait for what `after` (null: the null stream) holds so far.
 hipError_t start_after(hipStream_t after, const hipStream_t* streams, int count);
-// Several, into device buffers; status[i] for each i of which, *left: undecided.
+// Several, into device buffers, with one deadline for all; status[i] for each i
+// of which, *left: undecided.
 int run_bulk_batch(const mlmq_graph* const* graphs, const uint32_t* sources, uint32_t* const* dist_outs,
                    const mlmq_config* conf, const std::vector<int32_t>& which, hipStream_t after,
-                   uint32_t timeout_ms, int32_t* status, std::vector<int32_t>* left);
+                   uint32_t timeout_ms, int32_t* status, std::vector<int32_t>* left, uint32_t* left_ms);
 // What the host watchdog snapshots when a launch overruns its deadline.
 struct WatchdogView {
   const QueryCtrl* d_ctrl = nullptr;  // first query's control block

@@ -5,7 +5,6 @@
 
 #include <algorithm>
 #include <cstring>
-#include <memory>
 #include <mutex>
 #include <vector>
 
@@ -256,7 +255,7 @@ bool bulk_solves(const mlmq_graph* g, const mlmq_config& c, bool unit_weights) {
 }
 
 int run_bulk(const mlmq_graph* g, uint32_t source, uint32_t* dist_out, const mlmq_config& c, bool unit_weights,
-             bool dev_out, bool* finished) {
+             bool dev_out, bool* finished, uint32_t* left_ms) {
   Deadline deadline(c.timeout_ms);
   BulkSolve s;
   const int rc =
@@ -265,7 +264,13 @@ int run_bulk(const mlmq_graph* g, uint32_t source, uint32_t* dist_out, const mlm
   if (rc) return rc;
   s.begin();
   while (!s.advance()) __builtin_ia32_pause();
-  return s.finish(finished);
+  const int end = s.finish(finished);
+  *left_ms = deadline.left_ms();
+  if (!*finished && !*left_ms) {
+    *finished = true;
+    return set_error(MLMQ_ERR_TIMEOUT, "the solve overran its timeout of %u ms", deadline.ms());
+  }
+  return end;
 }
 
 namespace {
@@ -277,7 +282,7 @@ class BulkGroup {
   // Takes queries from which[*next] on while they are of one kind and fit.
   void begin(const mlmq_graph* const* graphs, const uint32_t* sources, uint32_t* const* dist_outs,
              const mlmq_config* conf, const std::vector<int32_t>& which, size_t* next, hipStream_t stream,
-             uint32_t timeout_ms, int32_t* status, std::vector<int32_t>* left);
+             Deadline* deadline, int32_t* status, std::vector<int32_t>* left);
   bool advance();
   // False: the stream did not get through; it must be left alone.
   bool finish(int32_t* status, std::vector<int32_t>* left);
@@ -291,7 +296,7 @@ class BulkGroup {
   bool tiled_ = false, late_ = false;
   uint32_t blocks_ = 0, limit_ = 0, issued_ = 0, spins_ = 0;
   hipError_t e_ = hipSuccess;
-  std::shared_ptr<Deadline> deadline_;
+  Deadline* deadline_ = nullptr;  // of the whole batch
 
   hipError_t launch(uint32_t i) {
     const uint32_t n = (uint32_t)solves_.size();
@@ -303,10 +308,10 @@ class BulkGroup {
 
 void BulkGroup::begin(const mlmq_graph* const* graphs, const uint32_t* sources, uint32_t* const* dist_outs,
                       const mlmq_config* conf, const std::vector<int32_t>& which, size_t* next, hipStream_t stream,
-                      uint32_t timeout_ms, int32_t* status, std::vector<int32_t>* left) {
+                      Deadline* deadline, int32_t* status, std::vector<int32_t>* left) {
   *this = BulkGroup();
   stream_ = stream;
-  deadline_ = std::make_shared<Deadline>(timeout_ms);
+  deadline_ = deadline;
   size_t bytes = 0;
   uint32_t most = 0, tiles = 0;
   while (*next < which.size() && solves_.size() < kGroup) {
@@ -314,10 +319,8 @@ void BulkGroup::begin(const mlmq_graph* const* graphs, const uint32_t* sources, 
     const mlmq_graph* g = graphs[i];
     const size_t mem = g->tiles ? tile_memory(g, false) : step_memory(g, g->d_ord_of != nullptr, false);
     if (!solves_.empty() && bytes + mem > kGroupBytes) break;
-    mlmq_config c = conf[i];
-    c.timeout_ms = timeout_ms;
     BulkSolve s;
-    const int rc = s.prepare(g, sources[i], dist_outs[i], c, stream, false, true, false, deadline_.get());
+    const int rc = s.prepare(g, sources[i], dist_outs[i], conf[i], stream, false, true, false, deadline_);
     if (s.no_room() && !solves_.empty()) break;  // as many as fit now, the others after them
     ++*next;
     if (rc) {
@@ -426,7 +429,8 @@ hipError_t start_after(hipStream_t after, const hipStream_t* streams, int count)
 // decided for come back in *left.
 int run_bulk_batch(const mlmq_graph* const* graphs, const uint32_t* sources, uint32_t* const* dist_outs,
                    const mlmq_config* conf, const std::vector<int32_t>& which, hipStream_t after,
-                   uint32_t timeout_ms, int32_t* status, std::vector<int32_t>* left) {
+                   uint32_t timeout_ms, int32_t* status, std::vector<int32_t>* left, uint32_t* left_ms) {
+  Deadline deadline(timeout_ms);
   std::vector<int32_t> of[kLanes];
   for (int32_t i : which)
     of[!graphs[i]->tiles ? 0 : (tile_kind(graphs[i]) < kTileLocalBits ? 1 : 2)].push_back(i);
@@ -444,17 +448,18 @@ int run_bulk_batch(const mlmq_graph* const* graphs, const uint32_t* sources, uin
   for (bool more = true; more;) {
     more = false;
     for (int k = 0; k < kLanes; ++k) {
-      if (stuck[k]) {
+      if (stuck[k] || (!group[k].busy() && deadline.over())) {
         for (; next[k] < of[k].size(); ++next[k])
-          status[of[k][next[k]]] = set_error(MLMQ_ERR_TIMEOUT, "the batch's stream did not get through in time");
+          status[of[k][next[k]]] = set_error(MLMQ_ERR_TIMEOUT, "the batch overran its timeout of %u ms", deadline.ms());
       }
       if (!group[k].busy() && next[k] < of[k].size())
-        group[k].begin(graphs, sources, dist_outs, conf, of[k], &next[k], streams->s[k], timeout_ms, status, left);
+        group[k].begin(graphs, sources, dist_outs, conf, of[k], &next[k], streams->s[k], &deadline, status, left);
       if (group[k].busy() && group[k].advance()) stuck[k] = !group[k].finish(status, left);
       more = more || group[k].busy() || next[k] < of[k].size();
     }
   }
   if (std::find(stuck, stuck + kLanes, true) == stuck + kLanes) streams_release(streams);
+  *left_ms = deadline.left_ms();
   return MLMQ_OK;
 }
 

@@ -39,6 +39,12 @@ class Deadline {
     const auto now = clk::now();
     return now > hard_ || (begun_ && now > end_);
   }
+  // What is left of the time, for the solver that goes on; 0: nothing.
+  uint32_t left_ms() const {
+    if (!begun_) return ms_;
+    const auto left = std::chrono::duration_cast<std::chrono::milliseconds>(end_ - clk::now()).count();
+    return left > 0 ? (uint32_t)left : 0u;
+  }
   // The device gets this long to be through with what it was given.
   clk::time_point drained_by() const { return std::max(hard_, clk::now()) + std::chrono::milliseconds(5000); }
 

@@ -224,3 +224,25 @@ def test_a_solve_does_not_wait_for_what_others_put_on_its_stream(sim):
     end.cancel()
     assert rc == 0 and took < 2.0, took
     np.testing.assert_array_equal(out, oracle.dijkstra(SKEWED, 3))
+
+
+def test_one_deadline_for_both_solvers(sim):
+    """A solve that runs out of steps leaves the queue worker what is left of its time."""
+    g = sim.graph(SKEWED)
+    p, out = sim.buffer(SKEWED.n)
+    sim.set(steps=10**6, step_ms=1, worker_ms=400)
+    for timeout, want in ((600, -5), (4000, 0)):
+        cfg = sim.config(g, timeout_ms=timeout)
+        assert sim.sssp(g, 3, p, cfg) == want
+        assert sim.batch([(g, 3, p)], [cfg])[0] == want
+    np.testing.assert_array_equal(out, oracle.dijkstra(SKEWED, 3))
+
+
+def test_one_deadline_for_all_groups_of_a_batch(sim):
+    g = sim.graph(MESH)
+    bufs = [sim.buffer(MESH.n) for _ in range(40)]
+    sim.set(step_ms=20)
+    rc, st = sim.batch([(g, i, b[0]) for i, b in enumerate(bufs)], [sim.config(g, timeout_ms=180)] * 40)
+    assert rc == -5 and st == [0] * 32 + [-5] * 8
+    for i in range(32):
+        np.testing.assert_array_equal(bufs[i][1], oracle.dijkstra(MESH, i))
