@@ -527,6 +527,8 @@ int slab_acquire(size_t dev_bytes, size_t host_bytes, Slab** out) {
     e = hipMalloc(&s->dev, s->dev_bytes);
     if (e == hipSuccess) e = hipHostMalloc(&s->host, s->host_bytes, hipHostMallocDefault);
     if (e != hipSuccess) {
+      // callers go on with less: the next launch must not report this error
+      (void)hipGetLastError();
       (void)hipFree(s->dev);
       delete s;
       return hip_fail(e, "allocating queue memory");

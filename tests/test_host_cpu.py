@@ -246,3 +246,21 @@ def test_one_deadline_for_all_groups_of_a_batch(sim):
     assert rc == -5 and st == [0] * 32 + [-5] * 8
     for i in range(32):
         np.testing.assert_array_equal(bufs[i][1], oracle.dijkstra(MESH, i))
+
+
+def test_no_room_for_a_bulk_solve(sim):
+    """Its lists do not fit, the queues do: the queue worker solves, alone and
+    in a batch beside a solve that has room."""
+    csr = gg.rmat(16, 2, seed=4)
+    big, small = sim.graph(csr), sim.graph(SKEWED)
+    (p, out), (q, other) = sim.buffer(csr.n), sim.buffer(SKEWED.n)
+    assert sim.sssp(small, 3, q) == 0
+    sim.set(largest=8 << 20, reset=1)
+    assert sim.sssp(big, 3, p) == 0, sim.error()
+    np.testing.assert_array_equal(out, oracle.dijkstra(csr, 3))
+    assert sim.count("worker") == 1
+    for order in ([(small, 3, q), (big, 4, p)], [(big, 4, p), (small, 3, q)]):
+        rc, st = sim.batch(order)
+        assert rc == 0 and not any(st), sim.error()
+        np.testing.assert_array_equal(out, oracle.dijkstra(csr, 4))
+        np.testing.assert_array_equal(other, oracle.dijkstra(SKEWED, 3))
