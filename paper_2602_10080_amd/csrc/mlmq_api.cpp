@@ -832,8 +832,9 @@ int run_single(const mlmq_graph* g, uint32_t source, uint32_t* dist_out, const m
   // are gathered back into the caller's order at the end
   const bool ordered = g->d_ord_of != nullptr;
   if (bulk_solves(g, c, unit_weights)) {
+    const BulkTurn turn;
     bool finished = false;
-    rc = run_bulk(g, source, dist_out, c, unit_weights, dev_out, &finished, &c.timeout_ms);
+    if (turn) rc = run_bulk(g, source, dist_out, c, unit_weights, dev_out, &finished, &c.timeout_ms);
     if (finished) return rc;
   }
   LaunchShape shape;

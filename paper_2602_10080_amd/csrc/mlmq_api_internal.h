@@ -121,6 +121,27 @@ void tile_destroy(mlmq_tiles* t);
 // Whether a solve on g with c runs as a sequence of launches (stepping or
 // tiled) instead of the queue worker.
 bool bulk_solves(const mlmq_graph* g, const mlmq_config& c, bool unit_weights);
+// Bulk solves and resident server kernels share the device only in turn. A
+// resident kernel holds three waves of 160 registers on three SIMDs of a CU
+// and two on the fourth; a step's workgroup (four waves of 64 registers) or a
+// tile's (eight of 48 and 39 to 131 KB of LDS) would wait for it to leave,
+// which under load it does not. So while one is there, or about to be, solves
+// take the queue worker, whose one-wave workgroups find room, and a server's
+// kernel starts when the bulk solves under way have ended.
+class BulkTurn {
+ public:
+  BulkTurn();
+  ~BulkTurn();
+  BulkTurn(const BulkTurn&) = delete;
+  BulkTurn& operator=(const BulkTurn&) = delete;
+  explicit operator bool() const { return mine_; }
+
+ private:
+  bool mine_;
+};
+void resident_begin();         // from here on no bulk solve begins
+bool resident_has_room();      // none is under way
+void resident_end();
 // Such a solve; *finished = false: nothing was decided, the queue worker must
 // solve in the *left_ms that are left of the deadline.
 int run_bulk(const mlmq_graph* g, uint32_t source, uint32_t* dist_out, const mlmq_config& c, bool unit_weights,

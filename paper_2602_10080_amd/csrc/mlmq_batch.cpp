@@ -219,19 +219,24 @@ extern "C" int mlmq_sssp_batch(const mlmq_graph* const* graphs, const uint32_t* 
   mlmq_config lc = conf[0];
   std::vector<int32_t> status((size_t)nq, MLMQ_OK);
   if (!bulk.empty()) {
-    uint32_t left = 0;
+    const BulkTurn turn;
     // largest first, so the long ones start early
     std::stable_sort(bulk.begin(), bulk.end(), [&](int32_t a, int32_t b) { return graphs[a]->m > graphs[b]->m; });
-    rc = run_bulk_batch(graphs, sources, dist_outs, conf.data(), bulk, reinterpret_cast<hipStream_t>(lc.stream),
-                        lc.timeout_ms, status.data(), &queues, &left);
-    if (rc) return rc;
+    const uint32_t all = lc.timeout_ms ? lc.timeout_ms : 60000, part = (all + 15) / 16;
+    uint32_t left = all;
+    if (turn) {
+      rc = run_bulk_batch(graphs, sources, dist_outs, conf.data(), bulk, reinterpret_cast<hipStream_t>(lc.stream),
+                          lc.timeout_ms, status.data(), &queues, &left);
+      if (rc) return rc;
+    } else {
+      queues.insert(queues.end(), bulk.begin(), bulk.end());
+    }
     if (!left) {
       for (int32_t i : queues) status[i] = MLMQ_ERR_TIMEOUT;
       queues.clear();
     }
     // in sixteenths, rounded up: the deadline is part of the captured launch,
     // which most calls can then replay
-    const uint32_t all = lc.timeout_ms ? lc.timeout_ms : 60000, part = (all + 15) / 16;
     lc.timeout_ms = std::min(all, (left + part - 1) / part * part);
   }
   if (!queues.empty()) {

@@ -250,6 +250,34 @@ int BulkSolve::deliver() {
   return rc;
 }
 
+namespace {
+std::mutex g_turn_mu;
+uint32_t g_resident = 0, g_under_way = 0;
+}  // namespace
+
+BulkTurn::BulkTurn() {
+  std::lock_guard<std::mutex> lk(g_turn_mu);
+  mine_ = g_resident == 0;
+  if (mine_) ++g_under_way;
+}
+BulkTurn::~BulkTurn() {
+  if (!mine_) return;
+  std::lock_guard<std::mutex> lk(g_turn_mu);
+  --g_under_way;
+}
+void resident_begin() {
+  std::lock_guard<std::mutex> lk(g_turn_mu);
+  ++g_resident;
+}
+bool resident_has_room() {
+  std::lock_guard<std::mutex> lk(g_turn_mu);
+  return g_under_way == 0;
+}
+void resident_end() {
+  std::lock_guard<std::mutex> lk(g_turn_mu);
+  --g_resident;
+}
+
 bool bulk_solves(const mlmq_graph* g, const mlmq_config& c, bool unit_weights) {
   return (g->tiles || g->step_ready) && is_default_choice(g, c, unit_weights);
 }

@@ -137,6 +137,8 @@ struct mlmq_server {
   uint32_t timeout_ms = 60000;
   uint64_t quit_ns = 0;
   bool cancel_sent = false;
+  bool resident = false;   // bulk solves keep away (BulkTurn)
+  uint64_t wait_ns = 0;    // since when the kernel waits for those under way
   bool leak = false;  // the device never let go of the server's memory
   bool stopping = false;        // stop flag raised on an idle server, kernel not yet gone
   uint64_t last_active_ns = 0;  // last time a query was pending or running
@@ -287,12 +289,23 @@ bool in_flight(const mlmq_server* s) {
   return false;
 }
 
+// How long the kernel waits for bulk solves under way (most take a few
+// milliseconds; one whose stream is held by other work may take any time, and
+// goes on when the kernel has left).
+constexpr uint64_t kTurnNs = 1000ull * 1000000ull;
+
 // Launches the resident kernel if queries are running and no wave is left.
 hipError_t keep_alive(mlmq_server* s) {
   if (!in_flight(s)) return hipSuccess;
   const hipError_t q = hipStreamQuery(s->ws);
   if (q == hipErrorNotReady) return hipSuccess;
   if (q != hipSuccess) return q;
+  if (!s->resident) {
+    resident_begin();
+    s->resident = true;
+    s->wait_ns = now_ns();
+  }
+  if (!resident_has_room() && now_ns() - s->wait_ns < kTurnNs) return hipSuccess;  // looked at again shortly
   s->launches += 1;
   return launch_server_worker(s->args, s->grid, s->lds, s->ws);
 }
@@ -317,6 +330,11 @@ hipError_t idle_stop(mlmq_server* s) {
     const hipError_t e = launch_server_signal(&s->d_ctl->stop.v, 0u, s->ws);
     if (e != hipSuccess) return e;
     s->stopping = false;
+  }
+  if (s->resident && quiet && !s->stopping && now - s->last_active_ns > kIdleStopNs &&
+      hipStreamQuery(s->ws) == hipSuccess) {
+    resident_end();
+    s->resident = false;
   }
   return hipSuccess;
 }
@@ -558,6 +576,7 @@ void mlmq_server_destroy(mlmq_server* s) {
     delete s;
     return;
   }
+  if (s->resident) resident_end();
   for (Slot& sl : s->slots)
     if (sl.ev) (void)hipEventDestroy(sl.ev);
   if (s->ws) (void)hipStreamDestroy(s->ws);

@@ -57,10 +57,9 @@ std::vector<std::string> g_log;
 bool g_logging = false;
 // How the stand-in kernels behave.
 uint32_t g_steps = 6;          // launches after which a bulk solve reports its end
-double g_worker_ms = 0, g_step_ms = 0;
+double g_worker_ms = 0, g_served_ms = 0, g_step_ms = 0;
 int g_resident = 0;            // server kernels on the device
 std::map<const void*, std::pair<const int32_t*, const uint64_t*>> g_tiled;  // id_of -> rows
-bool g_in_resident_ok = false;
 
 hipError_t err(hipError_t e) {
   if (e != hipSuccess && e != hipErrorNotReady) g_last = e;
@@ -429,7 +428,7 @@ hipError_t launch_server_worker(const ServerArgs& a, uint32_t, size_t, hipStream
       static std::map<const void*, Clock::time_point> began;
       auto& t = began[a.join + i];
       if (t == Clock::time_point()) t = Clock::now();
-      if (std::chrono::duration<double, std::milli>(Clock::now() - t).count() < g_worker_ms) continue;
+      if (std::chrono::duration<double, std::milli>(Clock::now() - t).count() < g_served_ms) continue;
       t = Clock::time_point();
       solve_query(a.slots[i]);
       a.join[i] = 0;
@@ -563,6 +562,7 @@ void sim_set(const char* what, double v) {
   const std::string w = what;
   if (w == "steps") g_steps = (uint32_t)v;
   if (w == "worker_ms") g_worker_ms = v;
+  if (w == "served_ms") g_served_ms = v;
   if (w == "step_ms") g_step_ms = v;
   if (w == "room") g_room = v < 0 ? ~size_t(0) : g_used + (size_t)v;
   if (w == "largest") g_largest = v < 0 ? ~size_t(0) : (size_t)v;

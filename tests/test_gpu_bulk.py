@@ -2,6 +2,7 @@
 solves) at the sizes and forms where their paths change, against the oracle.
 Distances are whole numbers: every comparison is exact."""
 import threading
+import time
 
 import numpy as np
 import pytest
@@ -137,3 +138,45 @@ def test_a_batch_starts_after_work_on_the_default_stream(queues):
         assert not any(status)
         for c, o in zip(graphs, outs):
             np.testing.assert_array_equal(host(o), expect(c, 3))
+
+
+def test_solves_and_batches_beside_a_busy_server():
+    """A server that always has queries keeps its kernel on the device; default
+    solves go on beside it and finish long before it would leave."""
+    served = gg.rmat(16, 16, seed=4)
+    h = mlmq.Graph.from_csr(served)
+    graphs = [gg.rmat(12, 16, seed=5), gg.grid(90, 90, 0.05, seed=3), gg.grid(30, 30, 0.0, seed=2)]
+    handles = [mlmq.Graph.from_csr(c) for c in graphs]
+    want = [expect(c, 3) for c in graphs]
+    outs = [mlmq.new_dist(served.n) for _ in range(8)]
+    srv = mlmq.Server([h], 1 << 30, max_slots=8)
+    stop, served_n = threading.Event(), []
+
+    def load():
+        while not stop.is_set():
+            for t in [srv.submit(0, 17 * k, outs[k]) for k in range(8)]:
+                assert srv.wait(t) == 0
+                served_n.append(t)
+
+    t = threading.Thread(target=load)
+    t.start()
+    try:
+        end = time.time() + 20
+        while not served_n and time.time() < end:
+            time.sleep(0.01)
+        for _ in range(3):
+            for c, g, w in zip(graphs, handles, want):
+                t0 = time.time()
+                np.testing.assert_array_equal(host(mlmq.sssp(g, 3)), w)
+                assert time.time() - t0 < 1.0
+            t0 = time.time()
+            res, status = mlmq.sssp_batch(handles, [3] * 3)
+            assert time.time() - t0 < 1.0 and not any(status)
+            for o, w in zip(res, want):
+                np.testing.assert_array_equal(host(o), w)
+    finally:
+        stop.set()
+        t.join()
+        srv.close()
+    assert served_n
+    np.testing.assert_array_equal(host(outs[0]), expect(served, 0))

@@ -87,9 +87,9 @@ def _sim():
 
 @pytest.fixture
 def sim(_sim):
-    _sim.set(steps=6, worker_ms=0, step_ms=0, room=-1, largest=-1, reset=1)
+    _sim.set(steps=6, worker_ms=0, served_ms=0, step_ms=0, room=-1, largest=-1, reset=1)
     yield _sim
-    _sim.set(steps=6, worker_ms=0, step_ms=0, room=-1, largest=-1)
+    _sim.set(steps=6, worker_ms=0, served_ms=0, step_ms=0, room=-1, largest=-1)
 
 
 ROAD = gg.grid(70, 80, 0.05, seed=1)      # several tiles
@@ -264,3 +264,78 @@ def test_no_room_for_a_bulk_solve(sim):
         assert rc == 0 and not any(st), sim.error()
         np.testing.assert_array_equal(out, oracle.dijkstra(csr, 4))
         np.testing.assert_array_equal(other, oracle.dijkstra(SKEWED, 3))
+
+
+class Server:
+    def __init__(self, sim, graphs):
+        self.sim, self.h = sim, ctypes.c_void_p()
+        arr = (ctypes.c_void_p * len(graphs))(*[g.value for g in graphs])
+        assert sim.lib.mlmq_server_create(arr, len(graphs), 1 << 28, 8, None, ctypes.byref(self.h)) == 0, sim.error()
+
+    def submit(self, k, src, p):
+        t = ctypes.c_uint64()
+        assert self.sim.lib.mlmq_server_submit(self.h, k, src, p, ctypes.byref(t)) == 0
+        return t.value
+
+    def wait(self, t):
+        return self.sim.lib.mlmq_server_wait(self.h, t, 20000)
+
+    def close(self):
+        self.sim.lib.mlmq_server_destroy(self.h)
+
+
+def _until(cond, limit=5.0):
+    t0 = time.time()
+    while not cond() and time.time() - t0 < limit:
+        time.sleep(0.002)
+    assert cond()
+
+
+def test_solves_beside_a_busy_server(sim):
+    """A resident kernel leaves no room for a bulk solve's workgroups: solves
+    take the queue worker until it has left."""
+    served, other = sim.graph(ROAD), sim.graph(SKEWED)
+    (p, _), (q, out) = sim.buffer(ROAD.n), sim.buffer(SKEWED.n)
+    srv = Server(sim, [served])
+    try:
+        sim.set(served_ms=1500, reset=1)
+        ticket = srv.submit(0, 3, p)
+        _until(lambda: sim.count("resident") == 1)
+        t0 = time.time()
+        assert sim.sssp(other, 5, q) == 0 and sim.batch([(other, 5, q)])[0] == 0
+        assert time.time() - t0 < 1.0 and sim.count("worker") == 2 and sim.count("step") == 0
+        np.testing.assert_array_equal(out, oracle.dijkstra(SKEWED, 5))
+        assert srv.wait(ticket) == 0
+        _until(lambda: sim.count("resident") == 0)
+
+        def bulk_again():
+            sim.set(reset=1)
+            return sim.sssp(other, 5, q) == 0 and sim.count("step") > 0
+        _until(bulk_again)
+    finally:
+        srv.close()
+    sim.set(reset=1)
+    assert sim.sssp(other, 5, q) == 0 and sim.count("step") > 0
+
+
+def test_a_server_kernel_waits_for_bulk_solves_under_way(sim):
+    served, other = sim.graph(ROAD), sim.graph(SKEWED)
+    (p, _), (q, out) = sim.buffer(ROAD.n), sim.buffer(SKEWED.n)
+    srv = Server(sim, [served])
+    try:
+        sim.set(steps=40, step_ms=5, reset=1)
+        took = []
+
+        def solve():
+            t0 = time.time()
+            took.append(sim.sssp(other, 5, q))
+            took.append(time.time() - t0)
+        t = threading.Thread(target=solve)
+        t.start()
+        _until(lambda: sim.count("step") > 3)
+        assert srv.wait(srv.submit(0, 3, p)) == 0
+        t.join()
+        assert took[0] == 0 and took[1] < 0.36, took  # 0.2 s of steps, not the server's idle time on top
+        np.testing.assert_array_equal(out, oracle.dijkstra(SKEWED, 5))
+    finally:
+        srv.close()
