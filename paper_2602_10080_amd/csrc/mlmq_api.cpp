@@ -236,8 +236,6 @@ void free_graph_arrays(mlmq_graph* g) {
   (void)hipFree(g->d_adj_ord);
   (void)hipFree(g->d_ord_of);
   (void)hipFree(g->d_sadj);
-  (void)hipFree(g->d_ioff);
-  (void)hipFree(g->d_iadj);
   tile_destroy(g->tiles);
   g->tiles = nullptr;
   g->d_ioff = nullptr;

@@ -39,7 +39,7 @@ struct mlmq_graph {
   // stepping solve (mlmq_step.cpp): copies in ascending weight class of the
   // out-rows and in-rows of the graph that plain solves run on
   bool step_ready = false;
-  uint64_t* d_sadj = nullptr;  // [m] out-rows
+  uint64_t* d_sadj = nullptr;  // [m] out-rows, in one allocation with
   int32_t* d_ioff = nullptr;   // [n+1] in-rows
   uint64_t* d_iadj = nullptr;  // [m]
   mlmq_tiles* tiles = nullptr;  // tiled copy (null: the graph does not fall into tiles)

@@ -134,30 +134,27 @@ hipError_t step_prepare(mlmq_graph* g) {
   // The sorted rows are a copy: the queue worker keeps the caller's edge order
   // (RMAT-20 with bucket queues: 60 ms in that order, 109 over sorted rows,
   // whose runs of equal weight all go to one bucket at a time).
-  uint64_t* raw = nullptr;
-  uint32_t* scratch = nullptr;
-  hipError_t e = hipMalloc(&g->d_sadj, 8ull * m);
-  if (e == hipSuccess) e = hipMalloc(&raw, 8ull * m);
-  if (e == hipSuccess) e = hipMalloc(&scratch, 4ull * (n + 1ull + n / 4096 + 2));
-  if (e == hipSuccess) e = hipMalloc(&g->d_ioff, 4ull * (n + 1ull));
-  if (e == hipSuccess) e = hipMalloc(&g->d_iadj, 8ull * m);
-  if (e == hipSuccess) e = launch_sort_rows(off, adj, g->d_sadj, n, shift, nullptr);
-  if (e == hipSuccess) e = launch_transpose(off, g->d_sadj, n, m, g->d_ioff, raw, scratch, nullptr);
-  if (e == hipSuccess) e = launch_sort_rows(g->d_ioff, raw, g->d_iadj, n, shift, nullptr);
-  if (e == hipSuccess) e = hipStreamSynchronize(nullptr);
-  (void)hipFree(raw);
-  (void)hipFree(scratch);
+  // One allocation and no temporaries: freeing one would wait for the device
+  // to be idle, which beside a resident server kernel it may not be for long. The
+  // unsorted in-rows stand where the sorted out-rows come last, and the cursors
+  // where the sorted in-rows do.
+  const size_t out_bytes = align_up(8ull * m, 256);
+  const size_t in_bytes = align_up(std::max(8ull * m, 4ull * (n + 1ull + n / 4096 + 2)), 256);
+  hipError_t e = hipMalloc(&g->d_sadj, out_bytes + in_bytes + 4ull * (n + 1ull));
   if (e != hipSuccess) {
-    (void)hipFree(g->d_sadj);
-    (void)hipFree(g->d_ioff);
-    (void)hipFree(g->d_iadj);
     g->d_sadj = nullptr;
-    g->d_ioff = nullptr;
-    g->d_iadj = nullptr;
     if (e != hipErrorOutOfMemory) return e;
     (void)hipGetLastError();  // no room for the copies: the graph keeps to the queue worker
     return hipSuccess;
   }
+  char* const base = reinterpret_cast<char*>(g->d_sadj);
+  g->d_iadj = reinterpret_cast<uint64_t*>(base + out_bytes);
+  g->d_ioff = reinterpret_cast<int32_t*>(base + out_bytes + in_bytes);
+  e = launch_transpose(off, adj, n, m, g->d_ioff, g->d_sadj, reinterpret_cast<uint32_t*>(g->d_iadj), nullptr);
+  if (e == hipSuccess) e = launch_sort_rows(g->d_ioff, g->d_sadj, g->d_iadj, n, shift, nullptr);
+  if (e == hipSuccess) e = launch_sort_rows(off, adj, g->d_sadj, n, shift, nullptr);
+  if (e == hipSuccess) e = hipStreamSynchronize(nullptr);
+  if (e != hipSuccess) return e;
   g->step_ready = true;
   return hipSuccess;
 }

@@ -4,6 +4,7 @@
 
 #include <algorithm>
 #include <cstring>
+#include <memory>
 #include <vector>
 
 #include "../../include/mlmq.h"
@@ -30,11 +31,13 @@ constexpr uint32_t kThreads = 512;  // of a workgroup: eight waves, two a SIMD
 size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
 // Tiles grown breadth-first, each from a vertex on the border of the ones
-// before, so that they are compact: a tile's vertices, and the vertices'
-// ids. False when the graph does not fall into such pieces: more than a
-// quarter of the edges would be cut.
+// before, so that they are compact: a tile's vertices, the vertices' ids, and
+// how many edges are cut or stand past a vertex's fourth inside its tile. False
+// when the graph does not fall into such pieces: more than a quarter of the
+// edges would be cut, or more tiles than a solve takes.
 bool cut_into_tiles(int32_t n, const int32_t* off, const int32_t* col, uint32_t sbits, uint32_t xcap,
-                    std::vector<uint32_t>* id_of, std::vector<uint32_t>* inv, std::vector<uint32_t>* verts) {
+                    std::vector<uint32_t>* id_of, std::vector<uint32_t>* inv, std::vector<uint32_t>* verts,
+                    uint64_t* cut_edges, uint64_t* extra_edges) {
   const uint32_t S = 1u << sbits;
   id_of->assign((size_t)n, kInf);
   inv->clear();
@@ -43,8 +46,9 @@ bool cut_into_tiles(int32_t n, const int32_t* off, const int32_t* col, uint32_t 
   std::vector<uint32_t> border, queue;
   size_t bh = 0;
   int32_t next = 0, left = n;
-  uint64_t edges = 0, cut = 0;
+  uint64_t edges = 0, cut = 0, extra = 0;
   while (left > 0) {
+    if (verts->size() == kTileMost) return false;
     const uint32_t t = (uint32_t)verts->size();
     const uint32_t base = t << sbits;
     uint32_t place = 0, ne = 0, nx = 0;
@@ -91,13 +95,23 @@ bool cut_into_tiles(int32_t n, const int32_t* off, const int32_t* col, uint32_t 
     verts->push_back(place);
     for (uint32_t i = 0; i < place; ++i) {
       const uint32_t v = (*inv)[(size_t)base + i];
-      for (int32_t e = off[v]; e < off[v + 1]; ++e) cut += ((*id_of)[(uint32_t)col[e]] >> sbits) != t;
+      uint32_t inside = 0;  // loops are left out
+      for (int32_t e = off[v]; e < off[v + 1]; ++e) {
+        const uint32_t u = (uint32_t)col[e];
+        if (((*id_of)[u] >> sbits) != t)
+          ++cut;
+        else if (u != v)
+          ++inside;
+      }
+      extra += inside > 4u ? inside - 4u : 0u;
     }
     edges += ne;
     // a graph without such pieces shows it at once
     if ((verts->size() >= 8 || left == 0) && 4 * cut > edges) return false;
     if (place == 0) return false;  // a row that fits no tile
   }
+  *cut_edges = cut;
+  *extra_edges = extra;
   return true;
 }
 
@@ -119,20 +133,21 @@ hipError_t tile_prepare(mlmq_graph* g, const int32_t* off, const int32_t* col) {
   const bool small = (uint32_t)g->n <= (1u << kTileLocalBits);
   const uint32_t sbits = small ? kTileLocalBits : 10u, xcap = small ? 4096u : 1024u;
   const uint32_t S = 1u << sbits;
-  if (g->m == 0 || g->max_w > kTileMaxWeight || (uint64_t)g->n > (1ull << 31)) return hipSuccess;
+  if (g->m == 0 || g->max_w > kTileMaxWeight || (uint32_t)g->n > kTileMostVertices) return hipSuccess;
   // few edges at every vertex, or a graph that is one tile
   if (small ? g->m > (int64_t)xcap + 4 * S : f.avg_deg > 4.8 || f.max_deg > 32) return hipSuccess;
   const size_t lds = tile_lds_bytes(sbits, xcap, kThreads);
   const DeviceInfo* di = device_info();
   if (lds > di->lds_per_wg) return hipSuccess;
   std::vector<uint32_t> inv, verts;
-  mlmq_tiles* t = new mlmq_tiles();
-  if (!cut_into_tiles(g->n, off, col, sbits, xcap, &t->id_of, &inv, &verts)) {
-    delete t;
-    return hipSuccess;
-  }
+  uint64_t cut = 0, extra = 0;
+  std::unique_ptr<mlmq_tiles> t(new mlmq_tiles());
+  if (!cut_into_tiles(g->n, off, col, sbits, xcap, &t->id_of, &inv, &verts, &cut, &extra)) return hipSuccess;
   const uint32_t tiles = (uint32_t)verts.size();
   const uint64_t ids = (uint64_t)tiles << sbits;
+  const uint32_t per_cu = std::max<uint32_t>(1, std::min<uint32_t>(4, (uint32_t)(di->lds_per_cu / lds)));
+  t->blocks = std::min<uint32_t>(tiles, per_cu * (uint32_t)di->cus);
+  if (tiles > kTileVisits * t->blocks) return hipSuccess;
   size_t o = 0;
   auto take = [&o](size_t bytes) {
     const size_t at = o;
@@ -141,10 +156,18 @@ hipError_t tile_prepare(mlmq_graph* g, const int32_t* off, const int32_t* col) {
   };
   const size_t o_verts = take(4ull * tiles), o_xb = take(4ull * (tiles + 1)), o_cb = take(4ull * (tiles + 1));
   const size_t o_xoff = take(2ull * tiles * (S + 8)), o_id = take(4ull * g->n), o_edge = take(16ull * ids);
-  const size_t o_extra = take(4ull * g->m), o_cut = take(8ull * g->m);
-  void* tmp = nullptr;
+  const size_t o_extra = take(4ull * extra), o_cut = take(8ull * cut);
+  // Scratch from the solves' pool: freeing memory would wait for the device to
+  // be idle. No room for it or the copy: the graph keeps to the queue worker.
+  Slab* slab = nullptr;
+  if (slab_acquire(12ull * ids, 0, &slab) != MLMQ_OK) return hipSuccess;
+  void* const tmp = slab->dev;
   hipError_t e = hipMalloc(&t->mem, o);
-  if (e == hipSuccess) e = hipMalloc(&tmp, 12ull * ids);
+  if (e == hipErrorOutOfMemory) {
+    (void)hipGetLastError();
+    slab_release(slab);
+    return hipSuccess;
+  }
   if (e == hipSuccess) {
     char* const base = static_cast<char*>(t->mem);
     TileBuild b;
@@ -182,23 +205,11 @@ hipError_t tile_prepare(mlmq_graph* g, const int32_t* off, const int32_t* col) {
     t->g.sbits = sbits;
     t->g.xcap = xcap;
   }
-  (void)hipFree(tmp);
+  slab_release(slab);
   // the same bound for every graph: a smaller one never lowers a larger one's
   if (e == hipSuccess) e = tile_set_lds(di->lds_per_wg);
-  if (e != hipSuccess) {
-    tile_destroy(t);
-    if (e != hipErrorOutOfMemory) return e;
-    (void)hipGetLastError();  // no room for the second copy: the graph keeps to the queue worker
-    return hipSuccess;
-  }
-  const uint32_t per_cu = std::max<uint32_t>(1, std::min<uint32_t>(4, (uint32_t)(di->lds_per_cu / lds)));
-  t->blocks = std::min<uint32_t>(tiles, per_cu * (uint32_t)di->cus);
-  if (tiles > kTileMost || tiles > kTileVisits * t->blocks) {
-    tile_destroy(t);
-    return hipSuccess;
-  }
-  g->tiles = t;
-  return hipSuccess;
+  g->tiles = t.release();  // freed with the graph, on failure too
+  return e;
 }
 
 namespace {

@@ -16,7 +16,8 @@ namespace mlmq {
 constexpr uint32_t kTileLocalBits = 12;  // a packed edge: target in the tile, weight above it
 constexpr uint32_t kTileMaxWeight = (1u << 20) - 1u;
 constexpr uint32_t kTileRounds = 8192;   // launches of one solve
-constexpr uint32_t kTileMost = 16384;    // tiles of a graph
+constexpr uint32_t kTileMostVertices = 1u << 24;  // of a graph
+constexpr uint32_t kTileMost = 17408;    // tiles of a graph: those vertices in tiles that are 94% full
 constexpr uint32_t kTileQueue = 512;     // vertices of a wave's frontier
 constexpr uint32_t kTileVisits = 64;     // most tiles that a workgroup visits in a round
 

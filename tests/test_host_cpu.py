@@ -339,3 +339,27 @@ def test_a_server_kernel_waits_for_bulk_solves_under_way(sim):
         np.testing.assert_array_equal(out, oracle.dijkstra(SKEWED, 5))
     finally:
         srv.close()
+
+
+def test_a_graph_is_made_beside_a_busy_server(sim):
+    """Nothing that its creation does waits for the device to be idle (freeing
+    device memory does), and no memory beyond the graph's own stays with it."""
+    served = sim.graph(ROAD)
+    p, _ = sim.buffer(ROAD.n)
+    srv = Server(sim, [served])
+    try:
+        sim.set(served_ms=1500, reset=1)
+        ticket = srv.submit(0, 3, p)
+        _until(lambda: sim.count("resident") == 1)
+        t0 = time.time()
+        for csr in (ROAD, MESH, SKEWED):
+            used = sim.count("used")
+            g = sim.graph(csr)
+            # rows, then tiles (records of 16 bytes, ids, offsets, the few edges past the fourth and over a border) or
+            # rows out and in
+            assert sim.count("used") - used < 8 * csr.m + 4 * csr.n + 16 * csr.m + 32 * csr.n + (1 << 20)
+        assert time.time() - t0 < 1.0 and sim.count("hipFree") == 0
+        assert srv.wait(ticket) == 0
+    finally:
+        srv.close()
+    assert g
