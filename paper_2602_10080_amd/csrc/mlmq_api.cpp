@@ -338,7 +338,7 @@ extern "C" int mlmq_graph_create(int32_t n, int64_t m, const int32_t* row_offset
     e = upload_degree_order(g.get(), hoff, hcol, hw);
   }
   if (e == hipSuccess) e = tile_prepare(g.get(), hoff, hcol);
-  if (e == hipSuccess && !g->tiles) e = step_prepare(g.get());
+  if (e == hipSuccess && !g->tiles) e = step_prepare(g.get(), hoff, hcol);
   if (e != hipSuccess) {
     free_graph_arrays(g.get());
     return hip_fail(e, "uploading graph");

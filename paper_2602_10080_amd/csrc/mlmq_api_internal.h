@@ -3,6 +3,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <atomic>
 #include <cstddef>
 #include <cstdint>
 #include <mutex>
@@ -39,6 +40,10 @@ struct mlmq_graph {
   // stepping solve (mlmq_step.cpp): copies in ascending weight class of the
   // out-rows and in-rows of the graph that plain solves run on
   bool step_ready = false;
+  bool step_for[2] = {};  // weighted, unit: whether the steps are few (step_suits)
+  // Bulk solves that ran out of steps, rounds or lists, by weighted and unit:
+  // how many in a row, and how many of the next calls do without one.
+  mutable std::atomic<uint32_t> bulk_failed[2] = {}, bulk_skip[2] = {};
   uint64_t* d_sadj = nullptr;  // [m] out-rows, in one allocation with
   int32_t* d_ioff = nullptr;   // [n+1] in-rows
   uint64_t* d_iadj = nullptr;  // [m]
@@ -114,7 +119,7 @@ int run_single(const mlmq_graph* g, uint32_t source, uint32_t* dist_out, const m
 // Whether c is the library's own choice for g (a solve may then run without queues).
 bool is_default_choice(const mlmq_graph* g, const mlmq_config& c, bool unit_weights);
 // Rows in ascending weight class and a transposed copy, where g suits the stepping solve.
-hipError_t step_prepare(mlmq_graph* g);
+hipError_t step_prepare(mlmq_graph* g, const int32_t* off, const int32_t* col);
 // Tiled copy of g, where it falls into tiles (off, col: host CSR).
 hipError_t tile_prepare(mlmq_graph* g, const int32_t* off, const int32_t* col);
 void tile_destroy(mlmq_tiles* t);

@@ -73,6 +73,8 @@ void streams_release(Streams* t) {
 
 }  // namespace
 
+static void note_end(const mlmq_graph* g, bool unit_weights, bool done);
+
 hipError_t BulkSolve::launch(uint32_t i) {
   return g_->tiles ? launch_tiles(tile_, i, blocks_, stream_) : launch_step(step_, i, blocks_, stream_);
 }
@@ -189,6 +191,7 @@ int BulkSolve::finish(bool* finished, hipError_t waited) {
     rc = set_error(MLMQ_ERR_TIMEOUT, "the solve overran its timeout of %u ms", deadline_->ms());
   else
     *finished = false;  // out of launches, or a list ran over
+  if (done || !*finished) note_end(g_, unit_, done);
   for (hipEvent_t ev : {ev0_, evw_, ev1_})
     if (ev) (void)hipEventDestroy(ev);
   slab_release(slab_);
@@ -279,7 +282,26 @@ void resident_end() {
 }
 
 bool bulk_solves(const mlmq_graph* g, const mlmq_config& c, bool unit_weights) {
-  return (g->tiles || g->step_ready) && is_default_choice(g, c, unit_weights);
+  if (!(g->tiles || (g->step_ready && g->step_for[unit_weights])) || !is_default_choice(g, c, unit_weights))
+    return false;
+  std::atomic<uint32_t>& skip = g->bulk_skip[unit_weights];
+  for (uint32_t k = skip.load(); k;)
+    if (skip.compare_exchange_weak(k, k - 1)) return false;
+  return true;
+}
+
+// A solve that did not come to its end cost its launches (2.5 ms) on top of the
+// worker's time, and the next one on the graph most likely does as well (a long
+// tail on a power-law graph, 2000 vertices on RMAT-18: 7.5 ms by the worker alone, 10.5
+// with the attempt): the next 7 calls do without one, 63 after another failure,
+// and so on until one succeeds.
+static void note_end(const mlmq_graph* g, bool unit_weights, bool done) {
+  std::atomic<uint32_t>& failed = g->bulk_failed[unit_weights];
+  if (done) {
+    if (failed.load()) failed.store(0);
+    return;
+  }
+  g->bulk_skip[unit_weights].store(failed.fetch_add(1) ? 63u : 7u);
 }
 
 int run_bulk(const mlmq_graph* g, uint32_t source, uint32_t* dist_out, const mlmq_config& c, bool unit_weights,

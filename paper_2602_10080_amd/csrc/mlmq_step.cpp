@@ -12,6 +12,7 @@
 #include "mlmq_api_internal.h"
 #include "mlmq_drive.h"
 #include "mlmq_internal.h"
+#include "mlmq_shape.h"
 #include "mlmq_step.h"
 
 using namespace mlmq;
@@ -122,10 +123,30 @@ bool is_default_choice(const mlmq_graph* g, const mlmq_config& c, bool unit_weig
   return same_queues(c, d);
 }
 
-hipError_t step_prepare(mlmq_graph* g) {
+// Whether a graph is shallow enough for steps. A solve takes two to three
+// launches a hop, the queue worker a time that grows with the edges too; past
+// 320 launches the worker has to begin anew. ms by worker / steps (r: estimated
+// radius): triangulated meshes of 64^2 vertices (r 41) 0.39 / 0.51, 128^2 (123)
+// 0.98 / 1.22, 384^2 (328) 3.2 / 5.7; a 160^2 mesh with one vertex of degree 40
+// (220) 0.91 / 1.49; geometric graphs of 20,000 vertices (90) 0.89 / 1.29 and
+// 200,000 (252) 3.5 / 6.2; a ring with few chords (1973) 4.8 / 7.2; but cubes
+// with 26 neighbours 64^3 (70) 7.6 / 1.5, uniform graphs (15-60) 0.65 / 0.30 to
+// 1.5 / 0.6. Levels need a launch or two a hop: triangulated 64^2 0.44 / 0.45,
+// 128^2 1.36 / 1.06, 192^2 (172) 2.1 / 1.75, 384^2 4.1 / 6.7; 160^2 mesh 1.56 / 1.66.
+static bool step_suits(uint32_t radius, int64_t m, bool unit) {
+  if (radius <= 24) return true;
+  return unit ? radius <= 215 && m >= 750ll * radius : radius <= 100 && m >= 2200ll * radius;
+}
+
+hipError_t step_prepare(mlmq_graph* g, const int32_t* h_off, const int32_t* h_col) {
   g->step_ready = false;
   // meshes and road-like graphs (a handful of edges at every vertex) are deep
   if (g->m == 0 || g->features.max_deg <= 8) return hipSuccess;
+  // skewed graphs have hubs that most of the graph is a few hops from
+  const bool skewed = g->features.std_deg > g->features.avg_deg;
+  const uint32_t radius = skewed ? 0u : estimate_radius(g->n, h_off, h_col);
+  for (int unit = 0; unit < 2; ++unit) g->step_for[unit] = step_suits(radius, g->m, unit != 0);
+  if (!g->step_for[0] && !g->step_for[1]) return hipSuccess;
   const uint32_t n = (uint32_t)g->n, m = (uint32_t)g->m;
   const bool ordered = g->d_ord_of != nullptr;
   const int32_t* off = ordered ? g->d_off_ord : g->d_off;

@@ -20,6 +20,7 @@
 
 #include "hip/hip_runtime.h"
 #include "mlmq_internal.h"
+#include "mlmq_shape.h"
 #include "mlmq_step.h"
 #include "mlmq_tile.h"
 
@@ -574,6 +575,7 @@ double sim_get(const char* what) {
   if (!std::strcmp(what, "resident")) return g_resident;
   return (double)g_count[what];
 }
+uint32_t sim_radius(int32_t n, const int32_t* off, const int32_t* col) { return estimate_radius(n, off, col); }
 void sim_pump() {
   std::lock_guard<std::recursive_mutex> lk(g_mu);
   pump();

@@ -180,3 +180,25 @@ def test_solves_and_batches_beside_a_busy_server():
         srv.close()
     assert served_n
     np.testing.assert_array_equal(host(outs[0]), expect(served, 0))
+
+
+def test_a_shallow_graph_with_a_long_tail():
+    """Steps run out on the tail: the queue worker solves, and later calls and
+    batches, with and without another try, give the same."""
+    core, tail = gg.rmat(12, 16, seed=5), 3000
+    hub = gg.max_degree_vertex(core)
+    row = np.repeat(np.arange(core.n), core.degrees())
+    t = core.n + np.arange(tail)
+    u, v = np.concatenate([[hub], t[:-1]]), t
+    w = np.full(tail, 9)
+    csr = gg.from_edges(core.n + tail, np.concatenate([row, u, v]), np.concatenate([core.col, v, u]),
+                        np.concatenate([core.w, w, w]))
+    g = mlmq.Graph.from_csr(csr)
+    want, levels = expect(csr, 3), oracle.bfs(csr, 3)
+    for _ in range(10):
+        np.testing.assert_array_equal(host(mlmq.sssp(g, 3)), want)
+        np.testing.assert_array_equal(host(mlmq.bfs(g, 3)), levels)
+    outs, status = mlmq.sssp_batch([g] * 3, [3] * 3)
+    assert not any(status)
+    for o in outs:
+        np.testing.assert_array_equal(host(o), want)

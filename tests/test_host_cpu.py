@@ -228,13 +228,13 @@ def test_a_solve_does_not_wait_for_what_others_put_on_its_stream(sim):
 
 def test_one_deadline_for_both_solvers(sim):
     """A solve that runs out of steps leaves the queue worker what is left of its time."""
-    g = sim.graph(SKEWED)
     p, out = sim.buffer(SKEWED.n)
     sim.set(steps=10**6, step_ms=1, worker_ms=400)
     for timeout, want in ((600, -5), (4000, 0)):
-        cfg = sim.config(g, timeout_ms=timeout)
-        assert sim.sssp(g, 3, p, cfg) == want
-        assert sim.batch([(g, 3, p)], [cfg])[0] == want
+        g = sim.graph(SKEWED)
+        assert sim.sssp(g, 3, p, sim.config(g, timeout_ms=timeout)) == want
+        g = sim.graph(SKEWED)
+        assert sim.batch([(g, 3, p)], [sim.config(g, timeout_ms=timeout)])[0] == want
     np.testing.assert_array_equal(out, oracle.dijkstra(SKEWED, 3))
 
 
@@ -363,3 +363,71 @@ def test_a_graph_is_made_beside_a_busy_server(sim):
     finally:
         srv.close()
     assert g
+
+
+def _with_hubs(side, hubs, degree):
+    """A mesh some of whose vertices have edges to many others nearby."""
+    ids = np.arange(side * side).reshape(side, side)
+    u = [ids[:, :-1].ravel(), ids[:-1].ravel()]
+    v = [ids[:, 1:].ravel(), ids[1:].ravel()]
+    rng = np.random.default_rng(1)
+    for h in rng.integers(0, side * side, hubs):
+        u.append(np.full(degree, h))
+        v.append((h + rng.integers(-3 * side, 3 * side, degree)) % (side * side))
+    u, v = np.concatenate(u), np.concatenate(v)
+    return gg.from_edges(side * side, np.concatenate([u, v]), np.concatenate([v, u]), rng.integers(1, 256, 2 * len(u)))
+
+
+def test_radius_estimate(sim):
+    """Within a factor of two of half the diameter of meshes, small on graphs
+    that spread exponentially, whatever the order of their vertices."""
+    def radius(csr):
+        off, col = csr.off32(), np.ascontiguousarray(csr.col, dtype=np.int32)
+        return sim.lib.sim_radius(csr.n, ctypes.c_void_p(off.ctypes.data), ctypes.c_void_p(col.ctypes.data))
+
+    def shuffled(csr):
+        p = np.random.default_rng(2).permutation(csr.n)
+        return gg.from_edges(csr.n, p[np.repeat(np.arange(csr.n), csr.degrees())], p[csr.col], csr.w)
+
+    for side in (40, 130, 300):
+        for csr in (gg.grid(side, side, 0.0, seed=1), gg.grid(side, side, 0.2, seed=1)):
+            for g in (csr, shuffled(csr)):
+                assert side / 2 <= radius(g) <= 4 * side
+    path = gg.from_edges(5000, np.arange(4999), np.arange(1, 5000), np.ones(4999))  # one way: seen from its vertices
+    assert 2500 <= radius(path) <= 10000
+    assert radius(gg.rmat(14, 16, seed=1)) <= 8
+    assert radius(gg.uniform(50000, 200000, seed=1)) <= 24
+    assert radius(gg.from_edges(3000, [0], [1], [1])) == 0
+    assert radius(gg.from_edges(1, [], [], [])) == 0
+
+
+def test_deep_graphs_do_not_begin_with_steps(sim):
+    """A mesh that one vertex's degree keeps out of tiles is too deep for steps."""
+    csr = _with_hubs(260, 1, 40)
+    g = sim.graph(csr)
+    p, out = sim.buffer(csr.n)
+    for bfs in (False, True):
+        sim.set(reset=1)
+        assert sim.sssp(g, 5, p, bfs=bfs) == 0
+        assert sim.count("step") == 0 and sim.count("worker") == 1
+
+
+def test_a_failed_bulk_solve_is_not_tried_again_at_once(sim):
+    g = sim.graph(SKEWED)
+    p, out = sim.buffer(SKEWED.n)
+    sim.set(steps=10**6)
+
+    def tries(calls, **kw):
+        n = 0
+        for _ in range(calls):
+            sim.set(reset=1)
+            assert sim.sssp(g, 5, p, **kw) == 0
+            n += sim.count("step") > 0
+        return n
+    assert tries(8) == 1 and tries(64) == 1 and tries(64) == 1
+    np.testing.assert_array_equal(out, oracle.dijkstra(SKEWED, 5))
+    assert tries(1, bfs=True) == 1  # levels have a count of their own
+    sim.set(steps=6)
+    assert tries(1) == 1 and tries(5) == 5  # it succeeds: every call again
+    sim.set(steps=10**6)
+    assert tries(8) == 1  # and the count starts over
