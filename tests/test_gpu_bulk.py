@@ -202,3 +202,16 @@ def test_a_shallow_graph_with_a_long_tail():
     assert not any(status)
     for o in outs:
         np.testing.assert_array_equal(host(o), want)
+
+
+def test_a_path_of_many_more_hops_than_rounds():
+    """100,000 hops: the tiled solve gets to the end by itself (a solve by
+    queues reports the time of its waves)."""
+    n = 100_000
+    rng = np.random.default_rng(2)
+    u, w = np.arange(n - 1), rng.integers(1, 256, n - 1)
+    csr = gg.from_edges(n, np.concatenate([u, u + 1]), np.concatenate([u + 1, u]), np.concatenate([w, w]))
+    g = mlmq.Graph.from_csr(csr)
+    out, st = mlmq.sssp(g, 0, stats=True)
+    np.testing.assert_array_equal(host(out), np.concatenate([[0], np.cumsum(w)]).astype(np.uint32))
+    assert st["wave_ms"] == 0
