@@ -135,7 +135,7 @@ bool is_default_choice(const mlmq_graph* g, const mlmq_config& c, bool unit_weig
 // 128^2 1.36 / 1.06, 192^2 (172) 2.1 / 1.75, 384^2 4.1 / 6.7; 160^2 mesh 1.56 / 1.66.
 static bool step_suits(uint32_t radius, int64_t m, bool unit) {
   if (radius <= 24) return true;
-  return unit ? radius <= 215 && m >= 750ll * radius : radius <= 100 && m >= 2200ll * radius;
+  return unit ? radius <= 215 && m >= 750ll * radius : radius <= 100 && m >= 4000ll * radius;
 }
 
 hipError_t step_prepare(mlmq_graph* g, const int32_t* h_off, const int32_t* h_col) {
