@@ -274,6 +274,33 @@ hipError_t upload_degree_order(mlmq_graph* g, const int32_t* off, const int32_t*
   return e;
 }
 
+// Cuts a graph into tiles on a thread of its own (a small one at once: there
+// the thread takes longer than the cut).
+class TileCutter {
+ public:
+  TileCutter(const mlmq_graph* g, const int32_t* off, const int32_t* col) {
+    if (g->n > 16384) {
+      try {
+        th_ = std::thread([=] { tiles_ = tile_cut(g, off, col); });
+        return;
+      } catch (...) {
+      }
+    }
+    tiles_ = tile_cut(g, off, col);
+  }
+  ~TileCutter() {
+    if (th_.joinable()) th_.join();
+  }
+  mlmq_tiles* wait() {
+    if (th_.joinable()) th_.join();
+    return tiles_;
+  }
+
+ private:
+  mlmq_tiles* tiles_ = nullptr;
+  std::thread th_;
+};
+
 }  // namespace
 
 extern "C" int mlmq_graph_create(int32_t n, int64_t m, const int32_t* row_offsets, const int32_t* col,
@@ -312,7 +339,6 @@ extern "C" int mlmq_graph_create(int32_t n, int64_t m, const int32_t* row_offset
   std::unique_ptr<mlmq_graph> g(new mlmq_graph());
   g->n = n;
   g->m = m;
-  compute_features(n, m, hoff, hw, &g->features, g->deg_hist);
   uint32_t maxw = 0, minw = kInf;
   for (int64_t e = 0; e < m; ++e) {
     maxw = std::max(maxw, hw[e]);
@@ -321,6 +347,9 @@ extern "C" int mlmq_graph_create(int32_t n, int64_t m, const int32_t* row_offset
   g->max_w = maxw;
   g->min_w = m ? minw : 1u;
   g->overflow_safe = (uint64_t)(n - 1) * (uint64_t)maxw < (uint64_t)kInf;
+  // tiles are cut while the features are computed and the rows packed and copied
+  TileCutter cutter(g.get(), hoff, hcol);
+  compute_features(n, m, hoff, hw, &g->features, g->deg_hist);
   g->sel_template = selector_pick(g->features);
   std::vector<uint64_t> adj((size_t)m);
   for (int64_t e = 0; e < m; ++e) adj[e] = (uint32_t)hcol[e] | ((uint64_t)hw[e] << 32);
@@ -337,7 +366,11 @@ extern "C" int mlmq_graph_create(int32_t n, int64_t m, const int32_t* row_offset
     adj.shrink_to_fit();
     e = upload_degree_order(g.get(), hoff, hcol, hw);
   }
-  if (e == hipSuccess) e = tile_prepare(g.get(), hoff, hcol);
+  mlmq_tiles* const tiles = cutter.wait();
+  if (e == hipSuccess)
+    e = tile_prepare(g.get(), tiles);
+  else
+    tile_destroy(tiles);
   if (e == hipSuccess && !g->tiles) e = step_prepare(g.get(), hoff, hcol);
   if (e != hipSuccess) {
     free_graph_arrays(g.get());

@@ -120,8 +120,10 @@ int run_single(const mlmq_graph* g, uint32_t source, uint32_t* dist_out, const m
 bool is_default_choice(const mlmq_graph* g, const mlmq_config& c, bool unit_weights);
 // Rows in ascending weight class and a transposed copy, where g suits the stepping solve.
 hipError_t step_prepare(mlmq_graph* g, const int32_t* off, const int32_t* col);
-// Tiled copy of g, where it falls into tiles (off, col: host CSR).
-hipError_t tile_prepare(mlmq_graph* g, const int32_t* off, const int32_t* col);
+// Tiled copy of g (off, col: host CSR): the cut, on the host alone, null where g
+// does not fall into tiles; then the copy on the device, which takes the cut over.
+mlmq_tiles* tile_cut(const mlmq_graph* g, const int32_t* off, const int32_t* col);
+hipError_t tile_prepare(mlmq_graph* g, mlmq_tiles* cut);
 void tile_destroy(mlmq_tiles* t);
 // Whether a solve on g with c runs as a sequence of launches (stepping or
 // tiled) instead of the queue worker.

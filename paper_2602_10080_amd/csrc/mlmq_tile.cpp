@@ -9,6 +9,7 @@
 
 #include "../../include/mlmq.h"
 #include "mlmq_api_internal.h"
+#include "mlmq_cut.h"
 #include "mlmq_drive.h"
 #include "mlmq_internal.h"
 #include "mlmq_tile.h"
@@ -17,7 +18,7 @@ using namespace mlmq;
 
 struct mlmq_tiles {
   TileGraph g{};
-  std::vector<uint32_t> id_of;  // [n] on the host (sources)
+  TileCut cut;                  // ids on the host (sources)
   void* mem = nullptr;          // one allocation behind g's arrays
   uint32_t blocks = 0;          // workgroups that fit on the device at once
 };
@@ -27,93 +28,9 @@ namespace mlmq {
 namespace {
 
 constexpr uint32_t kThreads = 512;  // of a workgroup: eight waves, two a SIMD
+constexpr uint32_t kCutThreads = 16;
 
 size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
-
-// Tiles grown breadth-first, each from a vertex on the border of the ones
-// before, so that they are compact: a tile's vertices, the vertices' ids, and
-// how many edges are cut or stand past a vertex's fourth inside its tile. False
-// when the graph does not fall into such pieces: more than a quarter of the
-// edges would be cut, or more tiles than a solve takes.
-bool cut_into_tiles(int32_t n, const int32_t* off, const int32_t* col, uint32_t sbits, uint32_t xcap,
-                    std::vector<uint32_t>* id_of, std::vector<uint32_t>* inv, std::vector<uint32_t>* verts,
-                    uint64_t* cut_edges, uint64_t* extra_edges) {
-  const uint32_t S = 1u << sbits;
-  id_of->assign((size_t)n, kInf);
-  inv->clear();
-  verts->clear();
-  std::vector<uint32_t> seen((size_t)n, 0u);  // tile + 1 whose queue a vertex was put in last
-  std::vector<uint32_t> border, queue;
-  size_t bh = 0;
-  int32_t next = 0, left = n;
-  uint64_t edges = 0, cut = 0, extra = 0;
-  while (left > 0) {
-    if (verts->size() == kTileMost) return false;
-    const uint32_t t = (uint32_t)verts->size();
-    const uint32_t base = t << sbits;
-    uint32_t place = 0, ne = 0, nx = 0;
-    inv->resize((size_t)base + S, kInf);
-    bool full = false;
-    while (!full && left > 0 && place < S - S / 4) {
-      int32_t seed = -1;
-      while (bh < border.size() && seed < 0) {
-        const uint32_t b = border[bh++];
-        if ((*id_of)[b] == kInf) seed = (int32_t)b;
-      }
-      if (seed < 0) {
-        while ((*id_of)[next] != kInf) ++next;
-        seed = next;
-      }
-      queue.clear();
-      queue.push_back((uint32_t)seed);
-      seen[seed] = t + 1u;
-      size_t qh = 0;
-      for (; qh < queue.size(); ++qh) {
-        const uint32_t v = queue[qh];
-        const uint32_t deg = (uint32_t)(off[v + 1] - off[v]);
-        const uint32_t over = deg > 4u ? deg - 4u : 0u;
-        if (place == S || nx + over > xcap) {
-          full = true;
-          break;
-        }
-        (*id_of)[v] = base + place;
-        (*inv)[(size_t)base + place] = v;
-        ++place;
-        --left;
-        ne += deg;
-        nx += over;
-        for (int32_t e = off[v]; e < off[v + 1]; ++e) {
-          const uint32_t u = (uint32_t)col[e];
-          if ((*id_of)[u] == kInf && seen[u] != t + 1u) {
-            seen[u] = t + 1u;
-            queue.push_back(u);
-          }
-        }
-      }
-      border.insert(border.end(), queue.begin() + (long)qh, queue.end());
-    }
-    verts->push_back(place);
-    for (uint32_t i = 0; i < place; ++i) {
-      const uint32_t v = (*inv)[(size_t)base + i];
-      uint32_t inside = 0;  // loops are left out
-      for (int32_t e = off[v]; e < off[v + 1]; ++e) {
-        const uint32_t u = (uint32_t)col[e];
-        if (((*id_of)[u] >> sbits) != t)
-          ++cut;
-        else if (u != v)
-          ++inside;
-      }
-      extra += inside > 4u ? inside - 4u : 0u;
-    }
-    edges += ne;
-    // a graph without such pieces shows it at once
-    if ((verts->size() >= 8 || left == 0) && 4 * cut > edges) return false;
-    if (place == 0) return false;  // a row that fits no tile
-  }
-  *cut_edges = cut;
-  *extra_edges = extra;
-  return true;
-}
 
 }  // namespace
 
@@ -123,27 +40,46 @@ void tile_destroy(mlmq_tiles* t) {
   delete t;
 }
 
-hipError_t tile_prepare(mlmq_graph* g, const int32_t* off, const int32_t* col) {
-  const mlmq_features& f = g->features;
-  // 1024 vertices a tile: four tiles fit a CU, loading one is short, and a round
-  // ends with its slowest tile (2048 x 2048 road-like grid: 1024 / 2048 / 4096
-  // vertices 7.0 / 7.2 / 8.0 ms; 611 x 1379 with detours 3.3 / 3.6 / 4.3). A
-  // graph that fits the largest tile is one tile: nothing is cut, and one round
-  // solves it.
-  const bool small = (uint32_t)g->n <= (1u << kTileLocalBits);
-  const uint32_t sbits = small ? kTileLocalBits : 10u, xcap = small ? 4096u : 1024u;
-  const uint32_t S = 1u << sbits;
-  if (g->m == 0 || g->max_w > kTileMaxWeight || (uint32_t)g->n > kTileMostVertices) return hipSuccess;
+namespace {
+
+// 1024 vertices a tile: four tiles fit a CU, loading one is short, and a round
+// ends with its slowest tile (2048 x 2048 road-like grid: 1024 / 2048 / 4096
+// vertices 7.0 / 7.2 / 8.0 ms; 611 x 1379 with detours 3.3 / 3.6 / 4.3). A
+// graph that fits the largest tile is one tile: nothing is cut, and one round
+// solves it.
+struct TileSize {
+  uint32_t sbits, xcap;
+};
+TileSize tile_size(const mlmq_graph* g) {
+  return (uint32_t)g->n <= (1u << kTileLocalBits) ? TileSize{kTileLocalBits, 4096u} : TileSize{10u, 1024u};
+}
+
+}  // namespace
+
+mlmq_tiles* tile_cut(const mlmq_graph* g, const int32_t* off, const int32_t* col) {
+  const TileSize z = tile_size(g);
+  if (g->m == 0 || g->max_w > kTileMaxWeight || (uint32_t)g->n > kTileMostVertices) return nullptr;
   // few edges at every vertex, or a graph that is one tile
-  if (small ? g->m > (int64_t)xcap + 4 * S : f.avg_deg > 4.8 || f.max_deg > 32) return hipSuccess;
-  const size_t lds = tile_lds_bytes(sbits, xcap, kThreads);
-  const DeviceInfo* di = device_info();
-  if (lds > di->lds_per_wg) return hipSuccess;
-  std::vector<uint32_t> inv, verts;
-  uint64_t cut = 0, extra = 0;
+  if (z.sbits == kTileLocalBits) {
+    if (g->m > (int64_t)z.xcap + (4ll << z.sbits)) return nullptr;
+  } else {
+    if ((double)g->m / g->n > 4.8) return nullptr;
+    for (int32_t v = 0; v < g->n; ++v)
+      if (off[v + 1] - off[v] > 32) return nullptr;
+  }
+  if (tile_lds_bytes(z.sbits, z.xcap, kThreads) > device_info()->lds_per_wg) return nullptr;
   std::unique_ptr<mlmq_tiles> t(new mlmq_tiles());
-  if (!cut_into_tiles(g->n, off, col, sbits, xcap, &t->id_of, &inv, &verts, &cut, &extra)) return hipSuccess;
-  const uint32_t tiles = (uint32_t)verts.size();
+  return cut_into_tiles(g->n, off, col, z.sbits, z.xcap, kTileMost, kCutThreads, &t->cut) ? t.release() : nullptr;
+}
+
+hipError_t tile_prepare(mlmq_graph* g, mlmq_tiles* of) {
+  std::unique_ptr<mlmq_tiles> t(of);
+  if (!t) return hipSuccess;
+  const TileCut& c = t->cut;
+  const uint32_t sbits = tile_size(g).sbits, xcap = tile_size(g).xcap, S = 1u << sbits;
+  const DeviceInfo* di = device_info();
+  const size_t lds = tile_lds_bytes(sbits, xcap, kThreads);
+  const uint32_t tiles = (uint32_t)c.verts.size();
   const uint64_t ids = (uint64_t)tiles << sbits;
   const uint32_t per_cu = std::max<uint32_t>(1, std::min<uint32_t>(4, (uint32_t)(di->lds_per_cu / lds)));
   t->blocks = std::min<uint32_t>(tiles, per_cu * (uint32_t)di->cus);
@@ -154,9 +90,9 @@ hipError_t tile_prepare(mlmq_graph* g, const int32_t* off, const int32_t* col) {
     o = align_up(o + bytes, 256);
     return at;
   };
-  const size_t o_verts = take(4ull * tiles), o_xb = take(4ull * (tiles + 1)), o_cb = take(4ull * (tiles + 1));
-  const size_t o_xoff = take(2ull * tiles * (S + 8)), o_id = take(4ull * g->n), o_edge = take(16ull * ids);
-  const size_t o_extra = take(4ull * extra), o_cut = take(8ull * cut);
+  const size_t o_verts = take(4ull * tiles), o_id = take(4ull * g->n), o_xb = take(4ull * (tiles + 1)), o_cb = take(4ull * (tiles + 1));
+  const size_t o_xoff = take(2ull * tiles * (S + 8)), o_edge = take(16ull * ids);
+  const size_t o_extra = take(4ull * c.extra), o_cut = take(8ull * c.cut);
   // Scratch from the solves' pool: freeing memory would wait for the device to
   // be idle. No room for it or the copy: the graph keeps to the queue worker.
   Slab* slab = nullptr;
@@ -186,9 +122,17 @@ hipError_t tile_prepare(mlmq_graph* g, const int32_t* off, const int32_t* col) {
     b.cut = reinterpret_cast<uint64_t*>(base + o_cut);
     b.tiles = tiles;
     b.sbits = sbits;
-    e = hipMemcpy(base + o_verts, verts.data(), 4ull * tiles, hipMemcpyHostToDevice);
-    if (e == hipSuccess) e = hipMemcpy(base + o_id, t->id_of.data(), 4ull * g->n, hipMemcpyHostToDevice);
-    if (e == hipSuccess) e = hipMemcpy(tmp, inv.data(), 4ull * ids, hipMemcpyHostToDevice);
+    if (g->n <= 65536) {  // one copy for both: a copy takes longer than its bytes
+      std::vector<uint32_t> both(o_id / 4 + (size_t)g->n);
+      std::copy(c.verts.begin(), c.verts.end(), both.begin());
+      std::copy(c.id_of.begin(), c.id_of.end(), both.begin() + (long)(o_id / 4));
+      e = hipMemcpy(base, both.data(), 4ull * both.size(), hipMemcpyHostToDevice);
+    } else {
+      e = hipMemcpy(base + o_verts, c.verts.data(), 4ull * tiles, hipMemcpyHostToDevice);
+      if (e == hipSuccess) e = hipMemcpy(base + o_id, c.id_of.data(), 4ull * g->n, hipMemcpyHostToDevice);
+    }
+    b.n = (uint32_t)g->n;
+    if (e == hipSuccess) e = launch_tile_ids(b, nullptr);
     if (e == hipSuccess) e = launch_tile_count(b, nullptr);
     if (e == hipSuccess) e = launch_tile_fill(b, nullptr);
     if (e == hipSuccess) e = hipStreamSynchronize(nullptr);
@@ -257,7 +201,7 @@ uint32_t tile_arguments(const mlmq_graph* g, char* base, uint32_t source, uint32
   a->active = reinterpret_cast<uint32_t*>(base + l.active);
   a->stats = reinterpret_cast<TileStats*>(base + l.stats);
   a->out = dev_out ? dist_out : reinterpret_cast<uint32_t*>(base + l.out);
-  a->source = t->id_of[source];
+  a->source = t->cut.id_of[source];
   // Width of a round: about a dozen hops of a mesh (light edges are taken, so a
   // hop is half a mean weight long). Wider, corrections that cross borders have
   // further to go; narrower, the launches count (2048 x 2048: 2 / 4 / 8 / 16

@@ -83,7 +83,7 @@ hipError_t tile_set_lds(size_t bytes);
 struct TileBuild {
   const int32_t* off;
   const uint64_t* adj;
-  const uint32_t* inv;
+  uint32_t* inv;
   const uint32_t* id_of;
   uint32_t* n_extra;  // [tiles << sbits] extra edges of a vertex, then their first place
   uint32_t* n_cut;    // the same for edges that leave the tile
@@ -93,8 +93,9 @@ struct TileBuild {
   uint32_t* edge;
   uint32_t* extra;
   uint64_t* cut;
-  uint32_t tiles, sbits;
+  uint32_t tiles, sbits, n;
 };
+hipError_t launch_tile_ids(const TileBuild& b, hipStream_t s);  // inv from id_of
 hipError_t launch_tile_count(const TileBuild& b, hipStream_t s);  // counts, places in the tile, bases
 hipError_t launch_tile_fill(const TileBuild& b, hipStream_t s);
 

@@ -440,6 +440,16 @@ __global__ void __launch_bounds__(256) mlmq_tile_init_many(const TileArgs* all) 
 
 // ------------------------------------------------------------ building the tiled copy
 
+// inv[id] = vertex of every id, kInf where a tile has none (it is filled first).
+__global__ void __launch_bounds__(256) mlmq_tile_blank(TileBuild b) {
+  const uint64_t ids = (uint64_t)b.tiles << b.sbits;
+  for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < ids; i += (uint64_t)gridDim.x * blockDim.x)
+    b.inv[i] = kInf32;
+}
+__global__ void __launch_bounds__(256) mlmq_tile_ids(TileBuild b) {
+  for (uint64_t v = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; v < b.n; v += (uint64_t)gridDim.x * blockDim.x)
+    b.inv[b.id_of[v]] = (uint32_t)v;
+}
 // Edges of every vertex inside its tile past the first four, and across its
 // border (self-loops never improve a label and are left out).
 __global__ void __launch_bounds__(256) mlmq_tile_degrees(TileBuild b) {
@@ -553,6 +563,12 @@ hipError_t launch_tile_many(const TileArgs* d_args, uint32_t count, uint32_t rou
     hipLaunchKernelGGL(mlmq_tile_init_many, dim3(256, count), dim3(256), 0, s, d_args);
   else
     hipLaunchKernelGGL(mlmq_tile_round_many, dim3(blocks, count), dim3(threads), lds, s, d_args, round);
+  return hipGetLastError();
+}
+
+hipError_t launch_tile_ids(const TileBuild& b, hipStream_t s) {
+  hipLaunchKernelGGL(mlmq_tile_blank, dim3(1024), dim3(256), 0, s, b);
+  hipLaunchKernelGGL(mlmq_tile_ids, dim3(1024), dim3(256), 0, s, b);
   return hipGetLastError();
 }
 

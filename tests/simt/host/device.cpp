@@ -19,6 +19,7 @@
 #include <vector>
 
 #include "hip/hip_runtime.h"
+#include "mlmq_cut.h"
 #include "mlmq_internal.h"
 #include "mlmq_shape.h"
 #include "mlmq_step.h"
@@ -513,6 +514,9 @@ hipError_t launch_tile_many(const TileArgs* d, uint32_t n, uint32_t i, uint32_t,
     });
   return launched(s, bulk_launch("tile", i, rows));
 }
+hipError_t launch_tile_ids(const TileBuild&, hipStream_t s) {
+  return launched_now(s, [] {});
+}
 hipError_t launch_tile_count(const TileBuild& b, hipStream_t s) {
   return launched_now(s, [=] { g_tiled[b.id_of] = {b.off, b.adj}; });
 }
@@ -574,6 +578,18 @@ double sim_get(const char* what) {
   if (!std::strcmp(what, "used")) return (double)g_used;
   if (!std::strcmp(what, "resident")) return g_resident;
   return (double)g_count[what];
+}
+// info: tiles (0: refused), cut edges, extra edges
+void sim_cut(int32_t n, const int32_t* off, const int32_t* col, uint32_t sbits, uint32_t xcap, uint32_t most,
+             uint32_t threads, uint32_t* id_of, uint32_t* verts, uint64_t* info) {
+  TileCut c;
+  const bool ok = cut_into_tiles(n, off, col, sbits, xcap, most, threads, &c);
+  info[0] = ok ? c.verts.size() : 0;
+  info[1] = c.cut;
+  info[2] = c.extra;
+  if (!ok) return;
+  std::memcpy(id_of, c.id_of.data(), 4ull * n);
+  std::memcpy(verts, c.verts.data(), 4ull * c.verts.size());
 }
 uint32_t sim_radius(int32_t n, const int32_t* off, const int32_t* col) { return estimate_radius(n, off, col); }
 void sim_pump() {

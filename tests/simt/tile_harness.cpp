@@ -84,7 +84,7 @@ extern "C" void sim_tiles(uint32_t n, const int32_t* off, const uint64_t* adj, c
   std::memset(&b, 0, sizeof(b));
   b.off = off;
   b.adj = adj;
-  b.inv = inv;
+  b.inv = const_cast<uint32_t*>(inv);
   b.id_of = id_of;
   b.n_extra = n_extra.data();
   b.n_cut = n_cut.data();

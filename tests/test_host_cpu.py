@@ -431,3 +431,55 @@ def test_a_failed_bulk_solve_is_not_tried_again_at_once(sim):
     assert tries(1) == 1 and tries(5) == 5  # it succeeds: every call again
     sim.set(steps=10**6)
     assert tries(8) == 1  # and the count starts over
+
+
+def _cut(sim, csr, sbits=10, xcap=1024, most=17408, threads=16):
+    off, col = csr.off32(), np.ascontiguousarray(csr.col, dtype=np.int32)
+    ids, verts, info = np.zeros(csr.n, np.uint32), np.zeros(csr.n, np.uint32), np.zeros(3, np.uint64)
+    p = lambda x: ctypes.c_void_p(x.ctypes.data)  # noqa: E731
+    t0 = time.time()
+    sim.lib.sim_cut(csr.n, p(off), p(col), sbits, xcap, most, threads, p(ids), p(verts), p(info))
+    return ids, verts[:int(info[0])], info, time.time() - t0
+
+
+def _reordered(csr, seed=2):
+    p = np.random.default_rng(seed).permutation(csr.n)
+    return gg.from_edges(csr.n, p[np.repeat(np.arange(csr.n), csr.degrees())], p[csr.col], csr.w)
+
+
+@pytest.mark.parametrize("name", ["road", "shuffled road", "mesh", "small", "loops", "hub", "pieces"])
+def test_tiles_hold_every_vertex_once(sim, name):
+    rng = np.random.default_rng(3)
+    csr = {"road": lambda: gg.grid(600, 700, 0.2, seed=1), "shuffled road": lambda: _reordered(gg.grid(500, 500, 0.05, seed=1)),
+           "mesh": lambda: gg.grid(40, 5000, 0.0, seed=1), "small": lambda: gg.grid(64, 65, 0.0, seed=1),
+           "loops": lambda: gg.from_edges(9000, *(lambda a: (np.concatenate([a, a, a[:-1]]),
+                                                             np.concatenate([a, a, a[1:]]), np.ones(3 * len(a) - 1)))(np.arange(9000))),
+           "hub": lambda: _with_hubs(120, 3, 700),
+           "pieces": lambda: gg.from_edges(200000, *(lambda a: (a[a % 7 != 6], a[a % 7 != 6] + 1, np.ones((a % 7 != 6).sum())))(
+               np.arange(199999)))}[name]()
+    ids, verts, info, _ = _cut(sim, csr)
+    assert len(verts)
+    # ids are places of tiles: each once, the first of its tile's
+    tile, place = ids >> 10, ids & 1023
+    np.testing.assert_array_equal(np.bincount(tile, minlength=len(verts)), verts)
+    assert len(np.unique(ids)) == csr.n and (place < verts[tile]).all()
+    # what the lists are allocated for
+    row = np.repeat(np.arange(csr.n), csr.degrees())
+    inside = (tile[row] == tile[csr.col])
+    assert info[1] == (~inside).sum() and 4 * info[1] <= csr.m
+    loc = np.bincount(row[inside & (row != csr.col)], minlength=csr.n)
+    over = np.maximum(loc - 4, 0)
+    assert info[2] == over.sum() and np.bincount(tile, weights=over).max() <= 1024
+    # tiles are nearly full; the counts do not depend on the threads
+    assert len(verts) <= (1.35 if name in ("hub", "pieces") else 1.05) * csr.n / 1024 + 2
+    for threads in (1, 3):
+        assert (_cut(sim, csr, threads=threads)[2] == info).all()
+
+
+def test_graphs_that_do_not_fall_into_tiles(sim):
+    assert len(_cut(sim, gg.uniform(300000, 600000, 255, seed=1))[1]) == 0  # too many edges would be cut
+    assert len(_cut(sim, gg.grid(300, 300, 0.0, seed=1), most=50)[1]) == 0  # too many tiles
+    star = gg.from_edges(3000, np.zeros(2999, int), np.arange(1, 3000), np.ones(2999))
+    assert len(_cut(sim, star)[1]) == 0  # a row that fits no tile
+    one = gg.grid(64, 64, 0.0, seed=1)
+    assert _cut(sim, one, sbits=12, xcap=4096)[1].tolist() == [4096]
