@@ -172,3 +172,18 @@ def test_out_of_steps_is_reported(sim):
     csr = gg.from_edges(90, np.arange(89), np.arange(1, 90), np.ones(89))
     dist, ops, info = _solve(sim, csr, _prepared(sim, csr), 0, 1, limit=40, blocks=1)
     assert info[1] == 0 and len(ops) == 39
+
+
+def test_transpose_of_hub_rows(sim):
+    """Whole waves of edges to one column, beside others, and partly filled."""
+    for leaves in (1, 63, 64, 65, 1000):
+        k = np.arange(1, leaves + 1)
+        csr = gg.from_edges(leaves + 3, np.concatenate([k, k[::3], [0], k[:5]]),
+                            np.concatenate([0 * k, 0 * k[::3] + leaves + 1, [leaves + 2], k[::-1][:5]]),
+                            np.arange(1, leaves + len(k[::3]) + 2 + len(k[:5])))
+        off, adj, srt, ioff, iadj = _prepared(sim, csr)
+        row = np.repeat(np.arange(csr.n, dtype=np.uint64), csr.degrees())
+        col = adj & np.uint64(0xFFFFFFFF)
+        want = np.stack([col, row | (adj >> np.uint64(32) << np.uint64(32))])
+        got = np.stack([np.repeat(np.arange(csr.n, dtype=np.uint64), np.diff(ioff)), iadj])
+        assert np.array_equal(got[:, np.lexsort(got)], want[:, np.lexsort(want)])
