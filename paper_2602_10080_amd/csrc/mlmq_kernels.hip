@@ -150,6 +150,7 @@ struct Ctx {
   bool ovf;                  // a candidate distance overflowed
   bool hungry;               // this wave is counted in ctrl->hungry
   uint32_t idle;             // consecutive loop iterations without work
+  uint32_t waits;            // bucket rings: most waits of an idle wave between two looks
   uint64_t ct64_wave, ct64_idle;  // ticks on the query / idle (set when it ends)
   uint32_t ct[kNumCounters]; // per-wave counters
 };
@@ -1362,14 +1363,16 @@ __device__ __forceinline__ void run_query(Ctx& c) {
         // A look at bucket rings reads two lines of each ring past the caches;
         // three thousand idle waves doing so delay the working waves' atomics
         // on the same lines. The longer a wave has been idle and the higher
-        // its index, the longer it waits, up to 48 x 3.4 us: the first 64
-        // waves look as often as ever, so new work is met at once. 512 x 512
-        // road-like grid, 3072 waves: 61 ms without the wait, 47 / 37 / 30
-        // with (index >> 8, idle >> 4) / (>> 6, >> 4) / (>> 6, all); RMAT-18
-        // 50 and 40 ms, RMAT-20 58 and 47, a 64 x 64 mesh 2.4 and 2.1. One
-        // ring is two lines and a ticket, and keeps the short waits.
+        // its number among the query's waves, the longer it waits, up to 48 x 3.4
+        // us: the first 64 waves look as often as ever, so new work is met at once;
+        // of a query with a share of the launch's waves, that share of 64 (a batch
+        // of eight RMAT-14 2.0 ms so, 2.7 with 64 of each). 512 x 512 road-like
+        // grid, 3072 waves: 61 ms without the wait, 47 / 37 / 34 with (number >> 8,
+        // idle >> 4) / (>> 6, >> 4) / (>> 6, all); RMAT-18 50 and 40 ms, RMAT-20 58
+        // and 47, a 64 x 64 mesh 2.4 and 2.1. One ring is two lines and a ticket,
+        // and keeps the short waits.
         if (c.q.nrings > 1 && !c.pq) {
-          for (uint32_t k = min(blockIdx.x >> 6, c.idle); k; --k) __builtin_amdgcn_s_sleep(127);
+          for (uint32_t k = min(c.waits, c.idle); k; --k) __builtin_amdgcn_s_sleep(127);
         }
         t_idle += (uint64_t)wall_clock64() - t0;
         continue;
@@ -1388,18 +1391,19 @@ __device__ __forceinline__ void run_query(Ctx& c) {
 
 // Next query for this wave: queries are taken in order; each accepts up to
 // want_wgs workgroups over its lifetime.
-__device__ __forceinline__ uint32_t pick_query(const LaunchArgs& a) {
-  uint32_t q = kInf;
+__device__ __forceinline__ uint32_t pick_query(const LaunchArgs& a, uint32_t* rank) {
+  uint32_t q = kInf, r = 0;
   if (lane() == 0 && ld32(&a.batch->cancel.v) == 0) {
     for (uint32_t i = ld32(&a.batch->cursor.v); i < (uint32_t)a.nq; ++i) {
       const QueryDesc* d = a.queries + i;
-      if (ld32(&d->ctrl->terminate.v) == 0 && add32(&d->ctrl->joined.v, 1u) < d->want_wgs) {
+      if (ld32(&d->ctrl->terminate.v) == 0 && (r = add32(&d->ctrl->joined.v, 1u)) < d->want_wgs) {
         q = i;
         break;
       }
       cas32(&a.batch->cursor.v, i, i + 1);
     }
   }
+  *rank = lane_val(r, 0);
   return lane_val(q, 0);
 }
 
@@ -1409,8 +1413,10 @@ __device__ __forceinline__ uint32_t pick_query(const LaunchArgs& a) {
 // clearing, only their counters), no pending tickets, no counters.
 __device__ __forceinline__ void setup_ctx(Ctx& c, const QueryDesc& q, uint64_t* smem, uint32_t l1_cap_alloc,
                                           uint32_t two_alloc, uint32_t stage_alloc, const uint32_t* cancel,
-                                          uint64_t deadline, uint64_t cap_wait, uint32_t* beat_word, bool pq_kernel) {
+                                          uint64_t deadline, uint64_t cap_wait, uint32_t* beat_word, bool pq_kernel,
+                                          uint32_t rank = 0) {
   c.q = q;
+  c.waits = rank * max(1u, gridDim.x / max(1u, q.want_wgs)) >> 6;
   // pq_kernel is a literal at each kernel, so the ring-only variant drops
   // every priority-queue branch; the host launches the priority-queue
   // variant whenever a query of the launch uses priority queues
@@ -1514,11 +1520,12 @@ __device__ __forceinline__ void worker_body(const LaunchArgs& a) {
   uint32_t* const my_beat = a.beats ? a.beats + blockIdx.x : nullptr;
   for (;;) {
     beat(my_beat, kPtPick, 0);
-    const uint32_t qi = pick_query(a);
+    uint32_t rank;
+    const uint32_t qi = pick_query(a, &rank);
     if (qi == kInf) break;
     Ctx c;
     setup_ctx(c, a.queries[qi], smem, a.l1_cap, a.l1_two, a.stage, &a.batch->cancel.v, t0 + a.timeout_ticks,
-              a.cap_wait_ticks, my_beat, kPQ);
+              a.cap_wait_ticks, my_beat, kPQ, rank);
     run_query(c);
     flush_counters(c);
     if (lane() == 0) add32(&c.q.ctrl->finished.v, 1u);
@@ -1549,12 +1556,13 @@ __device__ __forceinline__ void server_body(const ServerArgs& a) {
     const uint32_t g = uni(wave_min(open ? slot_gen(w) : kInf));
     if (g != kInf) {
       const uint32_t s = first_lane(ballot(open && slot_gen(w) == g));
-      uint32_t won = 0;
+      uint32_t won = kInf;  // this wave's number on the query
       if (l == 0) {
         const uint64_t got = __hip_atomic_fetch_add(&a.join[s], 1ull, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
-        won = slot_open(got) ? 1u : 0u;
+        if (slot_open(got)) won = slot_joined(got);
       }
-      if (!lane_val(won, 0)) {
+      won = lane_val(won, 0);
+      if (won == kInf) {
         // lost the race: the slot filled or closed; look again after a pause
         ++idle;
         backoff(min(idle >> 2, 6u));
@@ -1566,7 +1574,7 @@ __device__ __forceinline__ void server_body(const ServerArgs& a) {
       const QueryDesc q = load_desc_coherent(a.slots + s);
       Ctx c;
       setup_ctx(c, q, smem, a.l1_cap, a.l1_two, a.stage, &a.ctl->cancel.v, (uint64_t)wall_clock64() + a.timeout_ticks,
-                a.cap_wait_ticks, nullptr, kPQ);
+                a.cap_wait_ticks, nullptr, kPQ, won);
       run_query(c);
       flush_counters(c);
       if (l == 0) {

@@ -215,3 +215,20 @@ def test_a_path_of_many_more_hops_than_rounds():
     out, st = mlmq.sssp(g, 0, stats=True)
     np.testing.assert_array_equal(host(out), np.concatenate([[0], np.cumsum(w)]).astype(np.uint32))
     assert st["wave_ms"] == 0
+
+
+def test_batches_of_bucket_queues():
+    """Queries on bucket rings whose waves are any of the launch's: each query
+    has waves that look for work at once, whatever workgroups they are. More
+    queries than run at a time, beside one that takes many waves."""
+    graphs = [gg.grid(256, 256, 0.05, seed=9)] + [gg.grid(40 + i, 50, 0.05, seed=i) for i in range(30)] + \
+             [gg.rmat(10, 8, seed=i) for i in range(6)]
+    handles = [mlmq.Graph.from_csr(c) for c in graphs]
+    cfg = mlmq.default_config(l0_rows=1, l1_type=2, l2_type=1, bmax=32, bnum=4, delta2_log2=7, delta1=128, l1_cap=256,
+                              th_hub=0)
+    for _ in range(2):  # the second launch replays the first one's graph
+        outs, status, stats = mlmq.sssp_batch(handles, [5] * len(handles), configs=[cfg] * len(handles), stats=True)
+        assert not any(status)
+        for c, o, st in zip(graphs, outs, stats):
+            np.testing.assert_array_equal(host(o), expect(c, 5))
+            assert st["l2_writes"] > 0 and st["wave_ms"] > 0
