@@ -247,8 +247,8 @@ int BulkSolve::deliver() {
     t.stats[kCtStale] = g_->tiles ? 0 : s[1];
     t.stats[kCtEdges] = g_->tiles ? s[1] : s[2];
     t.stats[kCtPushes] = g_->tiles ? s[2] : s[3];
-    t.stats[kCtAtomics] = g_->tiles ? s[2] : s[4];
-    fill_stats(c_.stats_out, t, ms, wms, g_->tiles ? blocks_ : blocks_ * kStepWaves, 0);
+    t.stats[kCtAtomics] = g_->tiles ? s[3] : s[4];
+    fill_stats(c_.stats_out, t, ms, wms, blocks_, 0);
   }
   return rc;
 }

@@ -27,14 +27,14 @@ struct TileHost {
   uint32_t state;      // 0 running, 1 done
   uint32_t max_label;  // largest finite label, with `state`
   uint32_t rounds;
-  uint64_t stats[5];   // expansions, edges, pushes, tile visits, passes
+  uint64_t stats[4];   // expansions, edges, pushes, atomics
 };
 
 // Work counters for mlmq_stats, one set per segment.
 struct alignas(128) TileStats {
-  uint64_t expansions, edges, pushes, visits, passes;
+  uint64_t expansions, edges, pushes, atomics;
   uint32_t inv_max;  // ~(largest finite label)
-  uint32_t pad[21];
+  uint32_t pad[23];
 };
 constexpr uint32_t kTileSegs = 64;
 

@@ -149,7 +149,7 @@ struct alignas(16) Quad {
 
 // Counters of a lane.
 struct Work {
-  uint32_t exp, edge, push, visit, pass;
+  uint32_t exp, edge, push, atom;
 };
 
 // One visit of tile t: everything pending below limit.
@@ -178,7 +178,7 @@ __device__ __forceinline__ void visit(const TileArgs& a, const Lds& l, uint32_t 
     if (tid == 0u) l_st(l.ctl + kCtlMin, kInf32);
   }
   __syncthreads();
-  uint32_t n_exp = 0, n_push = 0, passes = 0, left;
+  uint32_t left;
   uint16_t* const q = l.q + (tid >> 6) * kTileQueue;
   const Quad* const quad = reinterpret_cast<const Quad*>(l.edge);
   const uint32_t place = (1u << kTileLocalBits) - 1u;
@@ -230,13 +230,23 @@ __device__ __forceinline__ void visit(const TileArgs& a, const Lds& l, uint32_t 
             u = ex & place;
             nd = sat_add(d, a.unit_w ? 1u : ex >> kTileLocalBits);
             old = l_min(l.lab + u, nd);
+            if (a.count_work) {
+              work.edge += 1u;
+              work.atom += 1u;
+              work.push += nd < old ? 1u : 0u;
+            }
           }
           enqueue(q, head, tail, u, nd < min(old, limit));
         }
       }
-      n_exp += go ? 1u : 0u;
-      n_push += (n0 < o0) + (n1 < o1) + (n2 < o2) + (n3 < o3);
-      ++passes;
+      if (a.count_work && go) {
+        // entries that lead back to the vertex fill its record up
+        const uint32_t edges = (u0 != v) + (u1 != v) + (u2 != v) + (u3 != v);
+        work.exp += 1u;
+        work.edge += edges;
+        work.atom += edges;
+        work.push += (n0 < o0) + (n1 < o1) + (n2 < o2) + (n3 < o3);
+      }
       compiler_fence();
     }
     __syncthreads();
@@ -255,19 +265,14 @@ __device__ __forceinline__ void visit(const TileArgs& a, const Lds& l, uint32_t 
     const uint32_t d = l.done[(uint32_t)(c >> 52)];
     const uint32_t dst = (uint32_t)c;
     const uint32_t nd = sat_add(d, a.unit_w ? 1u : (uint32_t)(c >> 32) & kTileMaxWeight);
+    if (a.count_work) work.edge += d != kInf32 ? 1u : 0u;
     if (nd >= a.lab[dst]) continue;
+    if (a.count_work) work.atom += 1u;
     if (nd >= g_min(a.lab + dst, nd)) continue;
-    n_push += 1u;
+    if (a.count_work) work.push += 1u;
     (void)g_min(key + (dst >> a.g.sbits), nd);
   }
   if (tid == 0u && left != kInf32) (void)g_min(key + t, left);
-  if (a.count_work) {
-    work.exp += n_exp;
-    work.edge += 4u * n_exp;
-    work.push += n_push;
-    work.visit += tid == 0u ? 1u : 0u;
-    work.pass += tid == 0u ? passes : 0u;
-  }
   __syncthreads();  // LDS is reused by the next tile
 }
 
@@ -334,9 +339,9 @@ __device__ __forceinline__ void tile_round_body(const TileArgs& a, uint32_t roun
     } else if (blockIdx.x == 0 && tid < 64u && uni(a.active[round - 2u]) != 0u) {
       const TileStats* s = a.stats + lane();
       const uint32_t inv = wave_min(s->inv_max);
-      uint64_t st[5] = {s->expansions, s->edges, s->pushes, s->visits, s->passes};
+      uint64_t st[4] = {s->expansions, s->edges, s->pushes, s->atomics};
 #pragma unroll
-      for (int i = 0; i < 5; ++i) {
+      for (int i = 0; i < 4; ++i) {
 #pragma unroll
         for (int o = 32; o; o >>= 1) {
           const uint32_t lo = __shfl_xor((uint32_t)st[i], o), hi = __shfl_xor((uint32_t)(st[i] >> 32), o);
@@ -346,7 +351,7 @@ __device__ __forceinline__ void tile_round_body(const TileArgs& a, uint32_t roun
       if (tid == 0u) {
         TileHost* h = a.host;
 #pragma unroll
-        for (int i = 0; i < 5; ++i)
+        for (int i = 0; i < 4; ++i)
           __hip_atomic_store(&h->stats[i], st[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
         __hip_atomic_store(&h->max_label, ~inv, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
         __hip_atomic_store(&h->rounds, round - 2u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
@@ -396,7 +401,7 @@ __device__ __forceinline__ void tile_round_body(const TileArgs& a, uint32_t roun
     }
     __syncthreads();
   }
-  Work work = {0, 0, 0, 0, 0};
+  Work work = {0, 0, 0, 0};
   for (uint32_t i = blockIdx.x, k = 0; i < total; i += gridDim.x, ++k)
     visit(a, l, uni(l.ctl[kCtlMine + k]), limit, next, work);
   if (a.count_work) {
@@ -404,8 +409,7 @@ __device__ __forceinline__ void tile_round_body(const TileArgs& a, uint32_t roun
     add_work(&s->expansions, work.exp);
     add_work(&s->edges, work.edge);
     add_work(&s->pushes, work.push);
-    add_work(&s->visits, work.visit);
-    add_work(&s->passes, work.pass);
+    add_work(&s->atomics, work.atom);
   }
 }
 
@@ -430,7 +434,7 @@ __device__ __forceinline__ void tile_init_body(const TileArgs& a) {
   }
   for (uint64_t i = tid; i < kTileSegs; i += stride) {
     TileStats* s = a.stats + i;
-    s->expansions = s->edges = s->pushes = s->visits = s->passes = 0ull;
+    s->expansions = s->edges = s->pushes = s->atomics = 0ull;
     s->inv_max = kInf32;
   }
 }

@@ -139,5 +139,5 @@ extern "C" void sim_tiles(uint32_t n, const int32_t* off, const uint64_t* adj, c
   info[0] = host.state;
   info[1] = host.rounds;
   info[2] = host.max_label;
-  for (int i = 0; i < 5; ++i) info[3 + i] = host.stats[i];
+  for (int i = 0; i < 4; ++i) info[3 + i] = host.stats[i];
 }

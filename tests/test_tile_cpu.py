@@ -104,3 +104,25 @@ def test_saturating_candidates(sim):
     want = np.where(fits < INF, fits, INF).astype(np.uint32)
     want[n - 1] = 7
     assert info[0] == 1 and np.array_equal(dist, want)
+
+
+@pytest.mark.parametrize("name", ["road", "multi", "star", "path"])
+def test_work_counters(sim, name):
+    """Edges that were looked at, not places of records: from one tile in one
+    round by one wave each vertex is expanded at least once, its edges counted
+    each time; a path has as many improvements as reached vertices."""
+    csr, src = GRAPHS[name]
+    cut = _cut(csr.n, 9, 512, None)
+    dist, info = _solve(sim, csr, src, cut, 9, 2**32 - 1, blocks=1, threads=64)
+    assert info[0] == 1
+    exp, edges, pushes, atomics = (int(x) for x in info[3:7])
+    reached = dist != INF
+    row = np.repeat(np.arange(csr.n), csr.degrees())
+    real = int((reached[row] & (csr.col != row)).sum())  # loops are not kept
+    assert exp >= reached.sum() and edges >= real and pushes >= reached.sum() - 1
+    assert edges == atomics  # inside a tile every candidate is an atomic
+    if name in ("star", "path"):  # nothing is expanded twice
+        assert exp == reached.sum() and edges == real and pushes == reached.sum() - 1
+    many, info = _solve(sim, csr, src, _cut(csr.n, 6, 64, None), 6, 2**32 - 1, threads=64)
+    exp, edges, pushes, atomics = (int(x) for x in info[3:7])
+    assert edges >= real and atomics <= edges and pushes <= atomics and pushes >= reached.sum() - 1
