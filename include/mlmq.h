@@ -360,11 +360,14 @@ int mlmq_select(const mlmq_graph* g, mlmq_config* out);
 /*
  * Autotuner (Section 3.5's input-adaptive configuration, measured): the
  * feature-driven default, then the templates in the selector's order, each
- * timed on three seeded sources (the highest-degree vertex and two drawn
- * among vertices with edges) until budget_ms is spent (0 = 2000); a candidate
- * may not run longer than 4x the best total so far. The fastest is cached for
- * the graph (used by cfg == NULL) and written to *out (nullable; struct_size
- * must be set; its stream, used for the timing runs, and stats_out are kept).
+ * timed on its queues on three seeded sources (the highest-degree vertex and
+ * two drawn among vertices with edges) until budget_ms is spent (0 = 2000); a
+ * candidate may not run longer than 4x the best total so far. The fastest is
+ * cached for the graph (what servers, queue batches and mlmq_sssp_noalloc run
+ * with cfg == NULL) and written to *out (nullable; struct_size must be set; its
+ * stream, used for the timing runs, and stats_out are kept). Then the bulk solve
+ * of the graph, where it has one, is timed on the same sources; plain solves and
+ * batches left to the library's choice go on with it unless the queues were faster.
  */
 int mlmq_autotune(mlmq_graph* g, uint32_t budget_ms, mlmq_config* out);
 

@@ -853,7 +853,8 @@ void heuristic_config(const mlmq_graph* g, mlmq_config* c) {
 }
 
 // One solve attempt sequence (with capacity retries) on a slab.
-int run_single(const mlmq_graph* g, uint32_t source, uint32_t* dist_out, const mlmq_config& cfg, bool unit_weights) {
+int run_single(const mlmq_graph* g, uint32_t source, uint32_t* dist_out, const mlmq_config& cfg, bool unit_weights,
+               bool queues_only) {
   int rc = check_config(&cfg);
   if (rc) return rc;
   mlmq_config c = cfg;
@@ -862,7 +863,7 @@ int run_single(const mlmq_graph* g, uint32_t source, uint32_t* dist_out, const m
   // power-law graphs are solved on their degree-ordered copy, whose labels
   // are gathered back into the caller's order at the end
   const bool ordered = g->d_ord_of != nullptr;
-  if (bulk_solves(g, c, unit_weights)) {
+  if (!queues_only && bulk_solves(g, c, unit_weights)) {
     const BulkTurn turn;
     bool finished = false;
     if (turn) rc = run_bulk(g, source, dist_out, c, unit_weights, dev_out, &finished, &c.timeout_ms);

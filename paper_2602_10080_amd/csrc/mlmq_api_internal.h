@@ -37,6 +37,7 @@ struct mlmq_graph {
   mlmq_config tuned{};
   int32_t sel_template = -1;  // the selector's top template (-1: the feature heuristic)
   mlmq_config sel_config{};   // that template as a configuration for this graph
+  bool queues_won = false;    // the tuner found queues faster than the bulk solve
   // stepping solve (mlmq_step.cpp): copies in ascending weight class of the
   // out-rows and in-rows of the graph that plain solves run on
   bool step_ready = false;
@@ -115,7 +116,7 @@ int status_to_code(uint32_t st);
 std::string describe_query_state(const QueryDesc& d, const uint32_t* d_beats, uint32_t nbeats);
 void fill_stats(mlmq_stats* st, const QueryCtrl& h, double ms, double worker_ms, uint32_t grid, uint32_t retries);
 int run_single(const mlmq_graph* g, uint32_t source, uint32_t* dist_out, const mlmq_config& c,
-               bool unit_weights = false);
+               bool unit_weights = false, bool queues_only = false);
 // Whether c is the library's own choice for g (a solve may then run without queues).
 bool is_default_choice(const mlmq_graph* g, const mlmq_config& c, bool unit_weights);
 // Rows in ascending weight class and a transposed copy, where g suits the stepping solve.

@@ -307,7 +307,9 @@ extern "C" int mlmq_autotune(mlmq_graph* g, uint32_t budget_ms, mlmq_config* out
   }
   // Candidates: the feature-driven default, then the templates in the
   // selector's order (with no trained model, in list order). Each is timed on
-  // the sources until the budget is spent.
+  // the sources until the budget is spent, on its queues: servers, queue batches
+  // and the allocation-free solve run what is chosen on nothing else. Whether
+  // default solves need queues at all is settled afterwards.
   std::vector<int32_t> cand = {-1};
   for (int32_t t : ranked(g->features, nullptr)) cand.push_back(t);
   const auto t0 = std::chrono::steady_clock::now();
@@ -338,7 +340,7 @@ extern "C" int mlmq_autotune(mlmq_graph* g, uint32_t budget_ms, mlmq_config* out
     double total = 0;
     bool okc = true;
     for (uint32_t s : srcs) {
-      if (run_single(g, s, d_dist, c) != MLMQ_OK) {
+      if (run_single(g, s, d_dist, c, false, true) != MLMQ_OK) {
         okc = false;
         break;
       }
@@ -349,14 +351,33 @@ extern "C" int mlmq_autotune(mlmq_graph* g, uint32_t budget_ms, mlmq_config* out
       best = keep;
     }
   }
-  (void)hipFree(d_dist);
   best.stats_out = nullptr;
   best.stream = nullptr;
   {
     std::lock_guard<std::mutex> lk(g->mu);
     g->tuned = best;
     g->has_tuned = true;
+    g->queues_won = false;
   }
+  // the bulk solve on the same sources, the second time each (the first one
+  // makes its scratch)
+  mlmq_config c = best;
+  mlmq_stats st;
+  std::memset(&st, 0, sizeof(st));
+  st.struct_size = sizeof(st);
+  c.stats_out = &st;
+  c.stream = out ? out->stream : nullptr;
+  double total = 0;
+  bool bulk = bulk_solves(g, c, false);
+  for (size_t i = 0; i < 2 * srcs.size() && bulk; ++i) {
+    bulk = run_single(g, srcs[i / 2], d_dist, c) == MLMQ_OK;
+    if (i & 1) total += st.kernel_ms;
+  }
+  if (bulk && total > best_ms) {
+    std::lock_guard<std::mutex> lk(g->mu);
+    g->queues_won = true;
+  }
+  (void)hipFree(d_dist);
   if (out) keep_caller_fields(out, best);
   return MLMQ_OK;
 }

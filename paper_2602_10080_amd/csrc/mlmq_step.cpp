@@ -109,13 +109,19 @@ static bool same_queues(const mlmq_config& a, const mlmq_config& b) {
          a.l2_capacity == b.l2_capacity && a.donate_min == b.donate_min && a.pnum == b.pnum;
 }
 
-// The queue configuration of a graph left to the library's choice is a
-// default, not a request: a solve that carries it may run without queues. Any
-// other configuration gets the queues it describes, and so does a deadline too
-// fine for the host to watch (the queue worker's waves watch it themselves).
+// The queue configuration of a graph left to the library's choice (the tuned
+// one where there is one) is a default, not a request: a solve that carries it
+// may run without queues, unless the tuner found queues to be faster. Any other
+// configuration gets the queues it describes, and so does a deadline too fine
+// for the host to watch (the queue worker's waves watch it themselves).
 bool is_default_choice(const mlmq_graph* g, const mlmq_config& c, bool unit_weights) {
   if (c.timeout_ms && c.timeout_ms < 50) return false;
-  mlmq_config d = g->sel_config;
+  mlmq_config d;
+  {
+    std::lock_guard<std::mutex> lk(const_cast<mlmq_graph*>(g)->mu);
+    if (g->has_tuned && g->queues_won) return false;
+    d = g->has_tuned ? g->tuned : g->sel_config;
+  }
   if (unit_weights) {
     d.delta1 = 1;
     d.delta2_log2 = 0;

@@ -483,3 +483,52 @@ def test_graphs_that_do_not_fall_into_tiles(sim):
     assert len(_cut(sim, star)[1]) == 0  # a row that fits no tile
     one = gg.grid(64, 64, 0.0, seed=1)
     assert _cut(sim, one, sbits=12, xcap=4096)[1].tolist() == [4096]
+
+
+@pytest.mark.parametrize("queues_faster", [False, True])
+def test_autotune_times_queues_and_keeps_the_faster_solver(sim, queues_faster):
+    """Every candidate is timed on its queues, whatever the budget; default
+    solves go on in bulk unless the queues were faster."""
+    for csr, kernel in ((ROAD, "tile"), (SKEWED, "step")):
+        for budget in (1, 300):
+            g = sim.graph(csr)
+            p, out = sim.buffer(csr.n)
+            before = sim.config(g).as_dict()
+            sim.set(worker_ms=1 if queues_faster else 10, step_ms=2 if queues_faster else 0, reset=1)
+            assert sim.lib.mlmq_autotune(g, budget, None) == 0
+            timed = sim.count("worker")
+            assert timed >= 3 and timed % 3 == 0
+            if budget == 300:  # the selector's own pick among them
+                assert timed >= 6
+            # six launches at least for each of two solves from three sources
+            assert sim.count(kernel) >= 36
+            for cfg in (None, sim.config(g)):
+                sim.set(reset=1)
+                assert sim.sssp(g, 5, p, cfg) == 0 and sim.batch([(g, 5, p)], [cfg] if cfg else None)[0] == 0
+                assert (sim.count(kernel) > 0, sim.count("worker") > 0) == (not queues_faster, queues_faster)
+                np.testing.assert_array_equal(out, oracle.dijkstra(csr, 5))
+            # what is no longer the default is a request for queues
+            old = sim.config(g)
+            for k, v in before.items():
+                setattr(old, k, v)
+            if old.as_dict() != sim.config(g).as_dict():
+                sim.set(reset=1)
+                assert sim.sssp(g, 5, p, old) == 0 and sim.count("worker") == 1
+
+
+def test_the_corpus_is_timed_on_queues(sim):
+    """Every template as collect.py asks for it, the graph's default among them."""
+    sys.path.insert(0, os.path.join(ROOT, "paper_2602_10080_amd", "selector"))
+    import collect
+    for csr in (ROAD, SKEWED):
+        g = sim.graph(csr)
+        p, _ = sim.buffer(csr.n)
+        cfgs = [sim.config(g)]
+        for t in range(-1, sim.lib.mlmq_candidate_count()):
+            c = sim.config(g)
+            assert sim.lib.mlmq_candidate_config(g, t, ctypes.byref(c)) == 0
+            cfgs.append(c)
+        for c in cfgs:
+            sim.set(reset=1)
+            assert sim.sssp(g, 3, p, collect.on_queues(c)) == 0, sim.error()
+            assert sim.count("worker") == 1
