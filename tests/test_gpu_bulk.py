@@ -232,3 +232,99 @@ def test_batches_of_bucket_queues():
         for c, o, st in zip(graphs, outs, stats):
             np.testing.assert_array_equal(host(o), expect(c, 5))
             assert st["l2_writes"] > 0 and st["wave_ms"] > 0
+
+
+def on_queues(cfg):
+    """cfg with a knob changed that its queues do not read: never the default."""
+    return cfg.copy(bmax=cfg.bmax // 2) if cfg.l2_type == 2 else cfg.copy(pnum=3)
+
+
+def overflowing(form, real):
+    """A graph in the form of one bulk solve whose largest distance fits, or
+    does not, below 2^32 - 1, beside sums that do not (Section 2.1)."""
+    if form == "tiles":  # a path of heavy edges over several tiles
+        n, w = 6000, (1 << 20) - 1
+        u = np.arange(n - 1)
+        fits = (2**32 - 2) // w  # hops
+        wt = np.full(n - 1, w, np.uint64)
+        if not real:
+            wt[fits:] = 1  # ends a little below the limit
+        return gg.from_edges(n, np.concatenate([u, u[:10]]), np.concatenate([u + 1, u[:10]]),
+                             np.concatenate([wt, wt[:10]])), n - 1
+    rng = np.random.default_rng(11)
+    n = 9000
+    u, v = rng.integers(0, n, 40000), rng.integers(0, n, 40000)
+    w = rng.integers(1, 1000, 40000)
+    # a way round by two edges whose sum is too large, and one vertex far out
+    tail = [2**31, 2**31 if real else 2**31 - 10**6]
+    # (the last vertex has no edges)
+    return gg.from_edges(n + 4, np.concatenate([u, [0, n, n + 1, n]]), np.concatenate([v, [n, n + 1, 1, n + 2]]),
+                         np.concatenate([w, [tail[0], tail[1], 2**32 - 1, 2**32 - 5]]) if real else
+                         np.concatenate([w, [tail[0], tail[1], 2**32 - 1, 7]])), n + 1
+
+
+@pytest.mark.parametrize("form", ["tiles", "steps"])
+@pytest.mark.parametrize("real", [False, True])
+def test_distances_near_the_largest_one(form, real):
+    csr, far = overflowing(form, real)
+    g = mlmq.Graph.from_csr(csr)
+    out, buf = mlmq.new_dist(csr.n), np.empty(csr.n, np.uint32)
+    if real:
+        for call in (lambda: mlmq.sssp(g, 0, out=out), lambda: mlmq.sssp(g, 0, out=buf)):
+            with pytest.raises(mlmq.MlmqError) as e:
+                call()
+            assert e.value.code == -3
+        _, status = mlmq.sssp_batch([g, g], [0, csr.n - 1], outs=[out, mlmq.new_dist(csr.n)])
+        assert status == [-3, 0]
+        return
+    want = expect(csr, 0)
+    assert want[far] != 0xFFFFFFFF and int(want[far]) + int(csr.w.max()) >= 2**32 - 1
+    out, st = mlmq.sssp(g, 0, out=out, stats=True)
+    assert st["wave_ms"] == 0  # no queues
+    np.testing.assert_array_equal(host(out), want)
+    np.testing.assert_array_equal(mlmq.sssp(g, 0, out=buf), want)
+    outs, status = mlmq.sssp_batch([g, g], [0, csr.n - 1])
+    assert status == [0, 0]
+    np.testing.assert_array_equal(host(outs[0]), want)
+    np.testing.assert_array_equal(host(outs[1]), expect(csr, csr.n - 1))
+
+
+def test_a_batch_of_bulk_solves_with_counters():
+    graphs = [gg.rmat(12, 16, seed=5), gg.grid(90, 90, 0.05, seed=3), gg.grid(30, 30, 0.0, seed=2)]
+    handles = [mlmq.Graph.from_csr(c) for c in graphs]
+    outs, status, stats = mlmq.sssp_batch(handles * 2, [3] * 6, stats=True)
+    assert not any(status)
+    for c, o, st in zip(graphs * 2, outs, stats):
+        want = expect(c, 3)
+        np.testing.assert_array_equal(host(o), want)
+        reached = int((want != 0xFFFFFFFF).sum())
+        assert st["expansions"] > 0 and st["edges"] > 0 and st["pushes"] >= reached // 2
+        assert st["wave_ms"] == st["l2_writes"] == st["l1_writes"] == 0
+
+
+def test_queue_batches_of_changing_layout():
+    """The captured launch of a batch on queues: the same number of queries with
+    queue memory laid out differently, and the same again."""
+    a, b = gg.grid(256, 256, 0.05, seed=41), gg.rmat(12, 8, seed=3)
+    ga, gb = mlmq.Graph.from_csr(a), mlmq.Graph.from_csr(b)
+    cfgs = [on_queues(ga.config()), on_queues(gb.config())]
+    for rep, mix in enumerate(([0, 0, 1], [0, 1, 1], [1, 1, 0], [0, 0, 1], [0, 0, 1])):
+        srcs = [(rep * 977 + 13 * i) % (a, b)[k].n for i, k in enumerate(mix)]
+        outs, status, stats = mlmq.sssp_batch([(ga, gb)[k] for k in mix], srcs, configs=[cfgs[k] for k in mix], stats=True)
+        assert not any(status)
+        for k, s, o, st in zip(mix, srcs, outs, stats):
+            np.testing.assert_array_equal(host(o), expect((a, b)[k], s), err_msg=str((rep, k, s)))
+            assert st["wave_ms"] > 0
+
+
+def test_queue_solves_on_a_degree_ordered_copy():
+    csr = gg.rmat(14, 16, seed=21)
+    g = mlmq.Graph.from_csr(csr, degree_order=True)
+    cfg = on_queues(g.config())
+    for s in [gg.max_degree_vertex(csr)] + [int(x) for x in gg.sample_sources(csr, 2, seed=4)]:
+        want = expect(csr, s)
+        out, st = mlmq.sssp(g, s, config=cfg, stats=True)
+        np.testing.assert_array_equal(host(out), want)
+        assert st["wave_ms"] > 0
+        np.testing.assert_array_equal(mlmq.sssp(g, s, out=np.empty(csr.n, np.uint32), config=cfg), want)
+        np.testing.assert_array_equal(host(mlmq.bfs(g, s, config=cfg.copy(delta1=1, delta2_log2=0))), oracle.bfs(csr, s))

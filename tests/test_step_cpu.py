@@ -187,3 +187,41 @@ def test_transpose_of_hub_rows(sim):
         want = np.stack([col, row | (adj >> np.uint64(32) << np.uint64(32))])
         got = np.stack([np.repeat(np.arange(csr.n, dtype=np.uint64), np.diff(ioff)), iadj])
         assert np.array_equal(got[:, np.lexsort(got)], want[:, np.lexsort(want)])
+
+
+@pytest.mark.parametrize("name,cap,phase_cost", [("rmat9", 64, 0), ("rmat9", 65, 0), ("rmat9", 96, 0), ("multi", 64, 0),
+                                                 ("multi", 65, 0), ("multi", 96, 0)])
+def test_an_overrun_list_is_rebuilt(sim, name, cap, phase_cost):
+    """A push that fills a segment of its list: the step's vertices are listed
+    again from the labels and the solve ends with the right ones."""
+    csr, src = GRAPHS[name]
+    prep, want = _prepared(sim, csr), oracle.dijkstra(csr, src)
+    seen = set()
+    for delta in (64, 256, 2**32 - 1):
+        for blocks in (1, 2):
+            dist, ops, info = _solve(sim, csr, prep, src, delta, cap=cap, blocks=blocks, limit=150, phase_cost=phase_cost)
+            if info[1] == 1:
+                assert np.array_equal(dist, want), (delta, ops)
+                seen |= set(ops)
+    assert RESCAN in seen
+
+
+def test_lists_too_small_to_rebuild_are_reported(sim):
+    csr, src = GRAPHS["rmat9"]
+    prep = _prepared(sim, csr)
+    for cap in (12, 17):
+        dist, ops, info = _solve(sim, csr, prep, src, 2**32 - 1, cap=cap, limit=60)
+        assert info[1] == 2, ops
+
+
+def test_a_task_table_that_runs_over(sim):
+    """Long rows whose tasks do not fit: the step is done again, or the solve
+    reports that it cannot; an answer is the right one."""
+    csr = _hubs(33000, 9000)
+    prep, outcomes = _prepared(sim, csr), []
+    for src, delta, task_cap in ((5, 20, 2), (0, 2**32 - 1, 4), (0, 2**32 - 1, 64)):
+        dist, ops, info = _solve(sim, csr, prep, src, delta, task_cap=task_cap, limit=60)
+        outcomes.append(int(info[1]))
+        if info[1] == 1:
+            assert np.array_equal(dist, oracle.dijkstra(csr, src)), (src, ops)
+    assert outcomes[-1] == 1 and outcomes[0] != 1
