@@ -1416,7 +1416,8 @@ __device__ __forceinline__ void setup_ctx(Ctx& c, const QueryDesc& q, uint64_t* 
                                           uint64_t deadline, uint64_t cap_wait, uint32_t* beat_word, bool pq_kernel,
                                           uint32_t rank = 0) {
   c.q = q;
-  c.waits = rank * max(1u, gridDim.x / max(1u, q.want_wgs)) >> 6;
+  const uint32_t queries = q.want_wgs ? gridDim.x / q.want_wgs : 1u;  // that share the launch like this one
+  c.waits = (queries ? rank * queries : rank) >> 6;
   // pq_kernel is a literal at each kernel, so the ring-only variant drops
   // every priority-queue branch; the host launches the priority-queue
   // variant whenever a query of the launch uses priority queues
