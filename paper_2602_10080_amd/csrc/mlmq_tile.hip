@@ -155,6 +155,8 @@ struct Work {
 // One visit of tile t: everything pending below limit.
 __device__ __forceinline__ void visit(const TileArgs& a, const Lds& l, uint32_t t, uint32_t limit, uint32_t* key,
                                       Work& work) {
+  // (in a group of solves the arguments are in memory: read once)
+  const bool unit = uni(a.unit_w) != 0u, count = uni(a.count_work) != 0u;
   const uint32_t S = 1u << a.g.sbits, tid = threadIdx.x, nt = blockDim.x;
   const uint32_t nv = uni(a.g.verts[t]);
   const uint64_t vb = (uint64_t)t << a.g.sbits;
@@ -204,10 +206,10 @@ __device__ __forceinline__ void visit(const TileArgs& a, const Lds& l, uint32_t 
       const Quad e = quad[v];
       const bool go = in && d < x;  // otherwise expanded at this label before
       const uint32_t u0 = e.x & place, u1 = e.y & place, u2 = e.z & place, u3 = e.w & place;
-      const uint32_t n0 = sat_add(d, a.unit_w ? 1u : e.x >> kTileLocalBits);
-      const uint32_t n1 = sat_add(d, a.unit_w ? 1u : e.y >> kTileLocalBits);
-      const uint32_t n2 = sat_add(d, a.unit_w ? 1u : e.z >> kTileLocalBits);
-      const uint32_t n3 = sat_add(d, a.unit_w ? 1u : e.w >> kTileLocalBits);
+      const uint32_t n0 = sat_add(d, unit ? 1u : e.x >> kTileLocalBits);
+      const uint32_t n1 = sat_add(d, unit ? 1u : e.y >> kTileLocalBits);
+      const uint32_t n2 = sat_add(d, unit ? 1u : e.z >> kTileLocalBits);
+      const uint32_t n3 = sat_add(d, unit ? 1u : e.w >> kTileLocalBits);
       uint32_t o0 = 0, o1 = 0, o2 = 0, o3 = 0;
       if (go) {
         l_st(l.done + v, d);
@@ -228,9 +230,9 @@ __device__ __forceinline__ void visit(const TileArgs& a, const Lds& l, uint32_t 
           if (k < x1) {
             const uint32_t ex = l.extra[k];
             u = ex & place;
-            nd = sat_add(d, a.unit_w ? 1u : ex >> kTileLocalBits);
+            nd = sat_add(d, unit ? 1u : ex >> kTileLocalBits);
             old = l_min(l.lab + u, nd);
-            if (a.count_work) {
+            if (count) {
               work.edge += 1u;
               work.atom += 1u;
               work.push += nd < old ? 1u : 0u;
@@ -239,7 +241,7 @@ __device__ __forceinline__ void visit(const TileArgs& a, const Lds& l, uint32_t 
           enqueue(q, head, tail, u, nd < min(old, limit));
         }
       }
-      if (a.count_work && go) {
+      if (count && go) {
         // entries that lead back to the vertex fill its record up
         const uint32_t edges = (u0 != v) + (u1 != v) + (u2 != v) + (u3 != v);
         work.exp += 1u;
@@ -264,12 +266,12 @@ __device__ __forceinline__ void visit(const TileArgs& a, const Lds& l, uint32_t 
     const uint64_t c = a.g.cut[i];
     const uint32_t d = l.done[(uint32_t)(c >> 52)];
     const uint32_t dst = (uint32_t)c;
-    const uint32_t nd = sat_add(d, a.unit_w ? 1u : (uint32_t)(c >> 32) & kTileMaxWeight);
-    if (a.count_work) work.edge += d != kInf32 ? 1u : 0u;
+    const uint32_t nd = sat_add(d, unit ? 1u : (uint32_t)(c >> 32) & kTileMaxWeight);
+    if (count) work.edge += d != kInf32 ? 1u : 0u;
     if (nd >= a.lab[dst]) continue;
-    if (a.count_work) work.atom += 1u;
+    if (count) work.atom += 1u;
     if (nd >= g_min(a.lab + dst, nd)) continue;
-    if (a.count_work) work.push += 1u;
+    if (count) work.push += 1u;
     (void)g_min(key + (dst >> a.g.sbits), nd);
   }
   if (tid == 0u && left != kInf32) (void)g_min(key + t, left);
