@@ -1363,14 +1363,16 @@ __device__ __forceinline__ void run_query(Ctx& c) {
         // A look at bucket rings reads two lines of each ring past the caches;
         // three thousand idle waves doing so delay the working waves' atomics
         // on the same lines. The longer a wave has been idle and the higher
-        // its number among the query's waves, the longer it waits, up to 48 x 3.4
-        // us: the first 64 waves look as often as ever, so new work is met at once;
-        // of a query with a share of the launch's waves, that share of 64 (a batch
-        // of eight RMAT-14 2.0 ms so, 2.7 with 64 of each). 512 x 512 road-like
-        // grid, 3072 waves: 61 ms without the wait, 47 / 37 / 34 with (number >> 8,
-        // idle >> 4) / (>> 6, >> 4) / (>> 6, all); RMAT-18 50 and 40 ms, RMAT-20 58
-        // and 47, a 64 x 64 mesh 2.4 and 2.1. One ring is two lines and a ticket,
-        // and keeps the short waits.
+        // its number, the longer it waits, up to 48 x 3.4 us: the first 64 waves
+        // look as often as ever, so new work is met at once. Alone, a query's waves
+        // are numbered by their place in the launch, which spreads the first ones
+        // over the device (in the order they join: 512 x 512 4% slower); where
+        // queries share the launch, in the order they join, and each query has its
+        // share of 64 (a batch of eight RMAT-14 2.0 ms so, 2.7 with 64 of each).
+        // 512 x 512 road-like grid, 3072 waves: 61 ms without the wait, 47 / 37 /
+        // 33 with (number >> 8, idle >> 4) / (>> 6, >> 4) / (>> 6, all); RMAT-18 50
+        // and 40 ms, RMAT-20 58 and 47, a 64 x 64 mesh 2.4 and 2.1. One ring is two
+        // lines and a ticket, and keeps the short waits.
         if (c.q.nrings > 1 && !c.pq) {
           for (uint32_t k = min(c.waits, c.idle); k; --k) __builtin_amdgcn_s_sleep(127);
         }
@@ -1526,7 +1528,7 @@ __device__ __forceinline__ void worker_body(const LaunchArgs& a) {
     if (qi == kInf) break;
     Ctx c;
     setup_ctx(c, a.queries[qi], smem, a.l1_cap, a.l1_two, a.stage, &a.batch->cancel.v, t0 + a.timeout_ticks,
-              a.cap_wait_ticks, my_beat, kPQ, rank);
+              a.cap_wait_ticks, my_beat, kPQ, a.nq == 1 ? blockIdx.x : rank);
     run_query(c);
     flush_counters(c);
     if (lane() == 0) add32(&c.q.ctrl->finished.v, 1u);
