@@ -149,6 +149,7 @@ class BulkTurn {
 };
 void resident_begin();         // from here on no bulk solve begins
 bool resident_has_room();      // none is under way
+bool resident_waits();         // a batch begins no further group
 void resident_end();
 // Such a solve; *finished = false: nothing was decided, the queue worker must
 // solve in the *left_ms that are left of the deadline.

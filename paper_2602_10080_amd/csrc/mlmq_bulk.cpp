@@ -276,6 +276,10 @@ bool resident_has_room() {
   std::lock_guard<std::mutex> lk(g_turn_mu);
   return g_under_way == 0;
 }
+bool resident_waits() {
+  std::lock_guard<std::mutex> lk(g_turn_mu);
+  return g_resident != 0;
+}
 void resident_end() {
   std::lock_guard<std::mutex> lk(g_turn_mu);
   --g_resident;
@@ -501,6 +505,11 @@ int run_bulk_batch(const mlmq_graph* const* graphs, const uint32_t* sources, uin
       if (stuck[k] || (!group[k].busy() && deadline.over())) {
         for (; next[k] < of[k].size(); ++next[k])
           status[of[k][next[k]]] = set_error(MLMQ_ERR_TIMEOUT, "the batch overran its timeout of %u ms", deadline.ms());
+      }
+      if (!group[k].busy() && next[k] < of[k].size() && resident_waits()) {
+        // a server's kernel waits for this batch: the rest goes on beside it
+        left->insert(left->end(), of[k].begin() + (long)next[k], of[k].end());
+        next[k] = of[k].size();
       }
       if (!group[k].busy() && next[k] < of[k].size())
         group[k].begin(graphs, sources, dist_outs, conf, of[k], &next[k], streams->s[k], &deadline, status, left);

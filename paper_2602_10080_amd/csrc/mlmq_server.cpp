@@ -289,10 +289,11 @@ bool in_flight(const mlmq_server* s) {
   return false;
 }
 
-// How long the kernel waits for bulk solves under way (most take a few
-// milliseconds; one whose stream is held by other work may take any time, and
-// goes on when the kernel has left).
-constexpr uint64_t kTurnNs = 1000ull * 1000000ull;
+// How long the kernel waits for bulk solves under way. Most take a few
+// milliseconds, a group of large ones a second; begun before their end, the
+// kernel would stop them. One whose stream is held by other work may take any
+// time, and goes on when the kernel has left.
+constexpr uint64_t kTurnNs = 10000ull * 1000000ull;
 
 // Launches the resident kernel if queries are running and no wave is left.
 hipError_t keep_alive(mlmq_server* s) {

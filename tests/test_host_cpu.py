@@ -532,3 +532,27 @@ def test_the_corpus_is_timed_on_queues(sim):
             sim.set(reset=1)
             assert sim.sssp(g, 3, p, collect.on_queues(c)) == 0, sim.error()
             assert sim.count("worker") == 1
+
+
+def test_a_batch_makes_room_for_a_server_between_its_groups(sim):
+    """The group under way ends as it is; what has not begun takes the queue
+    worker, and the server's kernel does not wait for the whole batch."""
+    served, mesh = sim.graph(ROAD), sim.graph(MESH)
+    p, _ = sim.buffer(ROAD.n)
+    bufs = [sim.buffer(MESH.n) for _ in range(70)]
+    srv = Server(sim, [served])
+    try:
+        sim.set(steps=20, step_ms=10, reset=1)  # 0.2 s a group of 32
+        res = []
+        t = threading.Thread(target=lambda: res.append(sim.batch([(mesh, i, b[0]) for i, b in enumerate(bufs)])))
+        t.start()
+        _until(lambda: sim.count("tile") > 3)
+        t0 = time.time()
+        assert srv.wait(srv.submit(0, 3, p)) == 0
+        assert time.time() - t0 < 0.35
+        t.join()
+        assert res[0][0] == 0 and not any(res[0][1]) and sim.count("worker") == 1
+        for i, (_p, o) in enumerate(bufs):
+            np.testing.assert_array_equal(o, oracle.dijkstra(MESH, i))
+    finally:
+        srv.close()
