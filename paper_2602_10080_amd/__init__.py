@@ -359,8 +359,10 @@ def _single(fn: str, graph: Graph, source: int, out, config: Optional[Config], s
 
 def sssp_batch(graphs: Sequence[Graph], sources: Sequence[int], outs=None,
                configs: Optional[Sequence[Optional[Config]]] = None, stream=None, stats: bool = False):
-    """Solve many (graph, source) queries in one persistent launch.
-    Returns (outs, statuses) or (outs, statuses, stats list)."""
+    """Solve many (graph, source) queries in one call: those left to the
+    library's choice as bulk solves in shared launches, the others in one
+    persistent launch. Starts after the work on stream (the current one if
+    None). Returns (outs, statuses) or (outs, statuses, stats list)."""
     nq = len(graphs)
     if len(sources) != nq:
         raise ValueError("graphs and sources differ in length")

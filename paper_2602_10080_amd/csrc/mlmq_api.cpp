@@ -410,8 +410,6 @@ extern "C" int mlmq_graph_info(const mlmq_graph* g, int32_t* n, int64_t* m, mlmq
 
 namespace mlmq {
 
-static size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
-
 // Queue memory of one query for a config.
 QueryPlan plan_query(const mlmq_graph* g, const mlmq_config& c, uint32_t extra_nb_log2, uint32_t hub_scale) {
   QueryPlan p;

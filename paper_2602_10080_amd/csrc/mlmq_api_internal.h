@@ -53,6 +53,8 @@ struct mlmq_graph {
 
 namespace mlmq {
 
+inline size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
+
 struct DeviceInfo {
   bool ok = false;
   int device = 0;

@@ -22,8 +22,6 @@ namespace {
 // Fewest waves a batched query is given when the batch is wide.
 constexpr uint32_t kBatchShare = 128;
 
-size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
-
 hipStream_t internal_stream() {
   static hipStream_t s = nullptr;
   static std::once_flag once;

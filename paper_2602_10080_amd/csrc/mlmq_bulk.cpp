@@ -19,8 +19,6 @@ namespace mlmq {
 
 namespace {
 
-size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
-
 // Groups of solves in flight at once in a batch: stepping ones, tiled ones and
 // tiled ones of graphs that are one tile.
 constexpr int kLanes = 3;

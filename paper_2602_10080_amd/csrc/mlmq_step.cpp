@@ -1,6 +1,5 @@
-// Host side of the stepping solve: preparation of a graph's rows, the rule
-// that picks the graphs, and the loop that keeps the device a few launches
-// ahead until a step reports the end.
+// Host side of the stepping solve: preparation of a graph's rows, the rules
+// that pick the graphs and the calls, and a solve's memory and arguments.
 
 #include <hip/hip_runtime.h>
 
@@ -20,8 +19,6 @@ using namespace mlmq;
 namespace mlmq {
 
 namespace {
-
-size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
 uint32_t class_shift(uint32_t max_w) {
   uint32_t bits = 0;

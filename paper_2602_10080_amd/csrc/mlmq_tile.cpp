@@ -1,4 +1,5 @@
-// Host side of the tiled solve: cutting a graph into tiles, and the rounds.
+// Host side of the tiled solve: which graphs are cut, their copy on the device,
+// and a solve's memory and arguments.
 
 #include <hip/hip_runtime.h>
 
@@ -29,8 +30,6 @@ namespace {
 
 constexpr uint32_t kThreads = 512;  // of a workgroup: eight waves, two a SIMD
 constexpr uint32_t kCutThreads = 16;
-
-size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
 }  // namespace
 
