@@ -69,9 +69,10 @@ extern "C" {
  * they return; a batch's queue solves, servers, mlmq_check, mlmq_latency_probe and mlmq_sssp_noalloc use the graph as given.
  * The copy costs the graph's memory once more plus 4 bytes per vertex.
  * Independent of that, a graph is also kept in the form of its bulk solve: tiles
- * (meshes and road-like graphs; about 24 bytes an edge) or rows in and out
- * sorted by weight (other graphs; 16 bytes an edge). A graph without room for
- * it is solved by queues alone.
+ * (meshes and road-like graphs; about 8 bytes an edge and 4 a vertex) or rows in and out
+ * sorted by weight (shallow graphs; 16 bytes an edge). Other graphs, and one
+ * without room for it, are solved by queues alone. Cutting tiles and sorting rows
+ * is part of mlmq_graph_create: it makes a mesh's creation 1.4 to 2.6 times as long.
  * MLMQ_GRAPH_KEEP_ORDER leaves the degree-ordered copy out; MLMQ_GRAPH_DEGREE_ORDER makes it for
  * any graph with edges. Setting both is an error.
  */
@@ -129,8 +130,11 @@ typedef struct mlmq_stats {
  *
  * A solve whose queue fields all equal the graph's default choice (cfg == NULL,
  * or mlmq_graph_config unchanged) and whose deadline is 0 or at least 50 ms runs
- * as a bulk solve, without queues, where the graph has a form for one. Any
- * other configuration runs on the queues it describes. The distances are the same.
+ * as a bulk solve, without queues, where the graph has a form for one, no
+ * server's kernel is on the device and the tuner has not found queues faster.
+ * Any other configuration runs on the queues it describes. The distances are the
+ * same. A bulk solve that does not get to its end (too many steps) is solved
+ * again on queues, and the next calls on that graph begin there.
  */
 typedef struct mlmq_config {
   uint32_t struct_size;
@@ -158,7 +162,7 @@ typedef struct mlmq_config {
   uint32_t grid_wgs;    /* persistent workgroups (0 = as many as fit on the device) */
   uint64_t l2_capacity; /* L2 elements per query (0 = automatic); grows on overflow */
   void* stream;         /* hipStream_t to run on (NULL = null stream) */
-  uint32_t timeout_ms;  /* device-side watchdog per solve (0 = 60000) */
+  uint32_t timeout_ms;  /* time allowed from the device's start, per solve or batch (0 = 60000) */
   uint32_t max_retries; /* capacity-overflow retries with a doubled L2 (default 3) */
   mlmq_stats* stats_out; /* nullable: receives counters of the solve */
   uint32_t donate_min;  /* spill threshold for idle waves: a wave whose L1 main (near) ring holds at
@@ -302,7 +306,8 @@ int mlmq_latency_probe(const mlmq_graph* g, uint32_t source, uint32_t hops, void
  * share one persistent launch. Query i solves graphs[i] from
  * sources[i] into dist_outs[i] (device memory, n_i uint32 each). cfgs may be
  * NULL (per-graph autotuned/default) or hold one config per query; launch
- * shape and stream come from cfgs[0] (or defaults). per_query_status may be
+ * shape, stream and timeout come from cfgs[0] (or defaults); the batch starts
+ * after the work that the stream (NULL: the null stream) holds. per_query_status may be
  * NULL or receive each query's status. Output per query is identical to
  * mlmq_sssp alone. Returns the first non-OK query status, else MLMQ_OK.
  */
