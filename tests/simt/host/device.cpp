@@ -55,11 +55,9 @@ std::map<uintptr_t, size_t> g_mem;  // device allocations
 std::map<uintptr_t, size_t> g_given;  // memory a test calls device memory
 size_t g_used = 0, g_room = ~size_t(0), g_largest = ~size_t(0);
 std::map<std::string, uint64_t> g_count;
-std::vector<std::string> g_log;
-bool g_logging = false;
 // How the stand-in kernels behave.
 uint32_t g_steps = 6;          // launches after which a bulk solve reports its end
-double g_worker_ms = 0, g_served_ms = 0, g_step_ms = 0;
+double g_worker_ms = 0, g_worker_more = 0, g_served_ms = 0, g_step_ms = 0;
 int g_resident = 0;            // server kernels on the device
 std::map<const void*, std::pair<const int32_t*, const uint64_t*>> g_tiled;  // id_of -> rows
 
@@ -74,10 +72,7 @@ SimStream* of(hipStream_t s) {
   }
   return s ? s : &g_null;
 }
-void note(const char* what) {
-  g_count[what] += 1;
-  if (g_logging) g_log.push_back(what);
-}
+void note(const char* what) { g_count[what] += 1; }
 
 void pump() {
   for (bool any = true; any;) {
@@ -182,6 +177,7 @@ void solve_query(const QueryDesc& q) {
   search(q.off, q.adj, q.n, q.source, q.unit_w, q.dist, &over);
   q.ctrl->error.v = kStOk;
   q.ctrl->overflow.v = over ? 1u : 0u;
+  q.ctrl->stats[kCtWaveTicks] = 1000000;  // 10 ms of waves: bulk solves report none
 }
 
 }  // namespace
@@ -381,6 +377,7 @@ hipError_t launch_init(const QueryDesc* q, BatchCtrl* b, int nq, uint32_t, hipSt
   });
 }
 hipError_t launch_worker(const LaunchArgs& a, uint32_t, uint32_t, size_t, hipStream_t s) {
+  g_worker_ms += g_worker_more;
   return launched(s, timed(g_worker_ms, [=] {
                     note("worker");
                     for (int i = 0; i < a.nq; ++i) {
@@ -567,6 +564,7 @@ void sim_set(const char* what, double v) {
   const std::string w = what;
   if (w == "steps") g_steps = (uint32_t)v;
   if (w == "worker_ms") g_worker_ms = v;
+  if (w == "worker_more") g_worker_more = v;  // each run takes that much longer than the last
   if (w == "served_ms") g_served_ms = v;
   if (w == "step_ms") g_step_ms = v;
   if (w == "room") g_room = v < 0 ? ~size_t(0) : g_used + (size_t)v;

@@ -87,9 +87,9 @@ def _sim():
 
 @pytest.fixture
 def sim(_sim):
-    _sim.set(steps=6, worker_ms=0, served_ms=0, step_ms=0, room=-1, largest=-1, reset=1)
+    _sim.set(steps=6, worker_ms=0, worker_more=0, served_ms=0, step_ms=0, room=-1, largest=-1, reset=1)
     yield _sim
-    _sim.set(steps=6, worker_ms=0, served_ms=0, step_ms=0, room=-1, largest=-1)
+    _sim.set(steps=6, worker_ms=0, worker_more=0, served_ms=0, step_ms=0, room=-1, largest=-1)
 
 
 ROAD = gg.grid(70, 80, 0.05, seed=1)      # several tiles
@@ -556,3 +556,21 @@ def test_a_batch_makes_room_for_a_server_between_its_groups(sim):
             np.testing.assert_array_equal(o, oracle.dijkstra(MESH, i))
     finally:
         srv.close()
+
+
+def test_autotune_beside_a_server(sim):
+    """No bulk solve can be timed there: default solves keep it."""
+    served, g = sim.graph(ROAD), sim.graph(SKEWED)
+    (p, _), (q, out) = sim.buffer(ROAD.n), sim.buffer(SKEWED.n)
+    srv = Server(sim, [served])
+    try:
+        sim.set(served_ms=2500, worker_ms=1, worker_more=0.5)  # later runs are slower than the candidates' first
+        ticket = srv.submit(0, 3, p)
+        _until(lambda: sim.count("resident") == 1)
+        assert sim.lib.mlmq_autotune(g, 20, None) == 0
+        assert srv.wait(ticket) == 0
+    finally:
+        srv.close()
+    sim.set(reset=1)
+    assert sim.sssp(g, 5, q) == 0 and sim.count("step") > 0
+    np.testing.assert_array_equal(out, oracle.dijkstra(SKEWED, 5))
