@@ -420,6 +420,7 @@ hipError_t launch_server_worker(const ServerArgs& a, uint32_t, size_t, hipStream
       *on = true;
       g_resident += 1;
       note("server kernel");
+      g_count["launches before it"] = g_count["step"] + g_count["tile"];
     }
     for (int i = 0; i < a.nslots; ++i) {
       const uint64_t w = a.join[i];

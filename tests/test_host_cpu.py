@@ -154,9 +154,9 @@ def test_deadline_counts_from_the_device_s_start(sim):
         out[:] = 1
         sim.lib.sim_hold(stream, 1)
         sim.lib.sim_fill(stream, p, ROAD.n, 7)
-        t = threading.Timer(0.3, sim.lib.sim_hold, (stream, 0))
+        t = threading.Timer(0.7, sim.lib.sim_hold, (stream, 0))
         t.start()
-        cfg = sim.config(g, stream=stream, timeout_ms=100)
+        cfg = sim.config(g, stream=stream, timeout_ms=300)
         rc = sim.sssp(g, 3, p, cfg) if call == "single" else sim.batch([(g, 3, p)], [cfg])[0]
         t.join()
         assert rc == 0, (call, sim.error())
@@ -241,8 +241,8 @@ def test_one_deadline_for_both_solvers(sim):
 def test_one_deadline_for_all_groups_of_a_batch(sim):
     g = sim.graph(MESH)
     bufs = [sim.buffer(MESH.n) for _ in range(40)]
-    sim.set(step_ms=20)
-    rc, st = sim.batch([(g, i, b[0]) for i, b in enumerate(bufs)], [sim.config(g, timeout_ms=180)] * 40)
+    sim.set(step_ms=100)  # 0.6 s a group
+    rc, st = sim.batch([(g, i, b[0]) for i, b in enumerate(bufs)], [sim.config(g, timeout_ms=900)] * 40)
     assert rc == -5 and st == [0] * 32 + [-5] * 8
     for i in range(32):
         np.testing.assert_array_equal(bufs[i][1], oracle.dijkstra(MESH, i))
@@ -324,18 +324,13 @@ def test_a_server_kernel_waits_for_bulk_solves_under_way(sim):
     srv = Server(sim, [served])
     try:
         sim.set(steps=40, step_ms=5, reset=1)
-        took = []
-
-        def solve():
-            t0 = time.time()
-            took.append(sim.sssp(other, 5, q))
-            took.append(time.time() - t0)
-        t = threading.Thread(target=solve)
+        got = []
+        t = threading.Thread(target=lambda: got.append(sim.sssp(other, 5, q)))
         t.start()
         _until(lambda: sim.count("step") > 3)
         assert srv.wait(srv.submit(0, 3, p)) == 0
         t.join()
-        assert took[0] == 0 and took[1] < 0.36, took  # 0.2 s of steps, not the server's idle time on top
+        assert got == [0] and sim.count("launches before it") == sim.count("step") >= 40
         np.testing.assert_array_equal(out, oracle.dijkstra(SKEWED, 5))
     finally:
         srv.close()
@@ -547,11 +542,10 @@ def test_a_batch_makes_room_for_a_server_between_its_groups(sim):
         t = threading.Thread(target=lambda: res.append(sim.batch([(mesh, i, b[0]) for i, b in enumerate(bufs)])))
         t.start()
         _until(lambda: sim.count("tile") > 3)
-        t0 = time.time()
         assert srv.wait(srv.submit(0, 3, p)) == 0
-        assert time.time() - t0 < 0.35
         t.join()
         assert res[0][0] == 0 and not any(res[0][1]) and sim.count("worker") == 1
+        assert 20 <= sim.count("launches before it") == sim.count("tile") < 40  # one group's
         for i, (_p, o) in enumerate(bufs):
             np.testing.assert_array_equal(o, oracle.dijkstra(MESH, i))
     finally:
