@@ -279,7 +279,7 @@ hipError_t upload_degree_order(mlmq_graph* g, const int32_t* off, const int32_t*
 class TileCutter {
  public:
   TileCutter(const mlmq_graph* g, const int32_t* off, const int32_t* col) {
-    if (g->n > 16384) {
+    if (g->n > 32768) {
       try {
         th_ = std::thread([=] { tiles_ = tile_cut(g, off, col); });
         return;

@@ -8,7 +8,7 @@ namespace mlmq {
 namespace {
 
 constexpr uint32_t kNone = 0xFFFFFFFFu;
-constexpr uint32_t kFirstTiles = 64;  // a graph that does not fall into tiles shows it in these, or
+constexpr uint32_t kFirstTiles = 16;  // a graph that does not fall into tiles shows it in these, or
 constexpr uint32_t kSomeTiles = 16;   // in one of every so many later ones
 
 // One pass grows the tiles, 16-21 ns a vertex (611 x 1379 and 2048 x 2048
